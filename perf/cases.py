@@ -395,15 +395,14 @@ def exact(case, seed):
     entries 9e-8 to 2e-6), so the codes, the factors, vhat's centres and k-means centres are left to
     the comparison within tolerance(); the operator P that they rest on is compared by apply_p and
     reconstruct."""
+    if case["op"] == "schedule" or case.get("lloyd"):
+        return None
     st, op = prepare(case, seed), case["op"]
     if op in ("quantize", "layer"):
         by_out = {id(it[4]): it[1] for grp in st["groups"] for it in grp}
         out = []
         for _, _, ce in st["out"]:
             w = by_out[id(ce)]
-            if case["lloyd"]:
-                out.append([None] * 4)
-                continue
             parts = [w[i:i + 2048] for i in range(0, w.shape[0], 2048)]
             if case["rot"]:
                 parts = [_rotate64(x, st["rot_seed"]) for x in parts]
@@ -411,8 +410,6 @@ def exact(case, seed):
         return out
     if op == "decompose":
         return [None, None, _u_steps64(st["w"]), None, None]
-    if op == "schedule":
-        return None
     if op == "optq":
         return [[None, None, _u_centers64(st["w_t"][: case["chunk"]]), None], None, None]
     if op == "apply_p":
