@@ -6,7 +6,8 @@ Run: python gen_tables.py > kashin_tables.h   (values are correctly rounded to f
 """
 import math
 
-RADICES = (3, 5, 7, 9, 12, 43)
+RADICES = (3, 5, 7, 25, 43)
+OUTER = (16, 20, 24, 32)  # outer radices with e^{i pi q / R} tables (compact eps factors)
 
 
 def fmt(v):
@@ -41,99 +42,13 @@ for b in (3, 43):
     print("template <> struct DctTab<%d> {" % b)
     print("  static constexpr float m[%d] = {%s};" % (b * b, ", ".join(vals)))
     print("};")
-
-
-def split_order(radix, nb=256):
-    """Order in which the 256 lanes of a split-pass sub-group take the nb = 256 butterflies j of
-    an inner pass of odd radix `radix` (stride 16, element slot i + (i >> 4)).  A lane reads slot
-    s(j) + const (32 lanes per LDS cycle: banks (j + (j >> 4)) mod 32) and writes element
-    16 R (j >> 4) + (j & 15) + 16 q (16 lanes per cycle: banks (j & 15) + R (j >> 4) + q mod 16).
-    Lanes in order 0..255 read with a two-way conflict in every 32-lane half; since the read
-    banks of the 256 butterflies do not cover the 32 residues evenly (7, 8 or 9 each), at best
-    seven halves are conflict-free and one absorbs the excess.  Built here: seven halves each take
-    every read bank once and every write bank twice (a bipartite b-matching by augmenting paths),
-    the last half the rest; each half splits into two 16-lane rows with distinct write banks."""
-    rd = lambda j: (j + (j >> 4)) % 32
-    wr = lambda j: ((j & 15) + radix * (j >> 4)) % 16
-    state = [12345]
-
-    def rnd(n):  # small LCG, so the table does not depend on the Python version
-        state[0] = (state[0] * 1103515245 + 12345) % (1 << 31)
-        return state[0] % n
-
-    def shuffled(v):
-        v = list(v)
-        for i in range(len(v) - 1, 0, -1):
-            k = rnd(i + 1)
-            v[i], v[k] = v[k], v[i]
-        return v
-
-    def half(avail):
-        by_rd = {}
-        for j in avail:
-            by_rd.setdefault(rd(j), []).append(j)
-        by_rd = {r: shuffled(v) for r, v in by_rd.items()}
-        chosen, holders = {}, {w: [] for w in range(16)}
-
-        def augment(r, seen):
-            for j in by_rd.get(r, []):
-                w = wr(j)
-                if w in seen:
-                    continue
-                seen.add(w)
-                if len(holders[w]) < 2:
-                    chosen[r] = j
-                    holders[w].append(r)
-                    return True
-                for r2 in list(holders[w]):
-                    old = chosen.pop(r2)
-                    holders[w].remove(r2)
-                    if augment(r2, seen):
-                        chosen[r] = j
-                        holders[w].append(r)
-                        return True
-                    chosen[r2] = old
-                    holders[w].append(r2)
-            return False
-
-        for r in shuffled(range(32)):
-            if not augment(r, set()):
-                return None
-        return [chosen[r] for r in range(32)]
-
-    for _ in range(1000):
-        avail, halves = set(range(nb)), []
-        for _h in range(nb // 32 - 1):
-            h = half(avail)
-            if h is None:
-                break
-            halves.append(h)
-            avail -= set(h)
-        if len(halves) == nb // 32 - 1:
-            halves.append(sorted(avail))
-            break
-    else:
-        raise RuntimeError("no split-pass order found")
-    order = []
-    for h in halves:
-        byw = {}
-        for j in h:
-            byw.setdefault(wr(j), []).append(j)
-        assert all(len(v) == 2 for v in byw.values()) and len(byw) == 16
-        order += [byw[w][0] for w in range(16)] + [byw[w][1] for w in range(16)]
-    assert sorted(order) == list(range(nb))
-    for k in range(nb // 32 - 1):
-        assert len({rd(j) for j in order[32 * k:32 * k + 32]}) == 32
-    for k in range(nb // 16):
-        assert len({wr(j) for j in order[16 * k:16 * k + 16]}) == 16
-    return order
-
-
-print("// lane order of the butterflies of a split inner pass of radix R (see split_order in gen_tables.py)")
-print("template <int R> struct SplitOrder;")
-for r in (43,):
-    o = split_order(r)
-    print("template <> struct SplitOrder<%d> {" % r)
-    print("  static constexpr unsigned char j[256] = {%s};" % ", ".join(str(v) for v in o))
+print("// cos/sin(pi q / R), q in [0, R)")
+print("template <int R> struct HalfTab;")
+for r in OUTER:
+    c = ", ".join(fmt(math.cos(math.pi * q / r)) for q in range(r))
+    s = ", ".join(fmt(math.sin(math.pi * q / r)) for q in range(r))
+    print("template <> struct HalfTab<%d> {" % r)
+    print("  static constexpr float c[%d] = {%s};" % (r, c))
+    print("  static constexpr float s[%d] = {%s};" % (r, s))
     print("};")
 print("}  // namespace kashin")

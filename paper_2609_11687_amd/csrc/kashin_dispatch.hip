@@ -4,26 +4,34 @@
 namespace kashin {
 
 // Supported vector lengths: N, threads per workgroup, occupancy target (waves per SIMD),
-// forward radices.
-#define KASHIN_SIZES(X)          \
-  X(64, 64, 2, 8, 8)                \
-  X(96, 64, 2, 16, 3, 2)            \
-  X(172, 64, 2, 4, 43)              \
-  X(256, 64, 2, 16, 16)             \
-  X(512, 64, 4, 8, 8, 8)            \
-  X(768, 64, 3, 16, 3, 16)          \
-  X(1024, 64, 2, 16, 4, 16)         \
-  X(2048, 128, 2, 16, 8, 16)        \
-  X(3072, 256, 3, 16, 12, 16)      \
-  X(4096, 256, 3, 16, 16, 16)       \
-  X(5120, 320, 3, 16, 16, 4, 5)     \
-  X(6144, 384, 3, 16, 16, 8, 3)     \
-  X(8192, 512, 2, 16, 16, 16, 2)    \
-  X(10000, 640, 3, 16, 5, 5, 5, 5)  \
-  X(11008, 768, 3, 16, 43, 16)      \
-  X(13824, 448, 2, 16, 16, 2, 3, 9) \
-  X(14336, 448, 2, 16, 16, 8, 7)    \
-  X(16384, 1024, 4, 16, 8, 8, 16)
+// forward radices.  From 256 up N = R0 M R0 on the three-pass path; quantising rows (k = 30, us)
+// against the shapes before it, which took four or five passes with the tables in memory:
+//   5120 (16384 rows)  21640 -> 9245     10000 (4096)  9150 -> 5180     14336 (4096) 11960 -> 6620
+//   6144 (8192)        12580 -> 5250     13824 (4096) 14900 -> 7200     16384 (4096)  9330 -> 6570
+//   8192 (8192)        14760 -> 5790     256 (8192)     472 -> 208
+// The occupancy target is the one that measured best per length: 128 registers (four waves) pay at
+// 5120 and 6144, whose five- and six-wave workgroups otherwise leave SIMDs short; at 4096 and
+// 3072 three waves without spills beat four with; 8192 takes 256 threads of 32 values, whose
+// inner pass keeps every wave busy, over 512 of 16 (y = P x: 195 against 311 us).
+#define KASHIN_SIZES(X)         \
+  X(64, 64, 2, 8, 8)            \
+  X(96, 64, 2, 16, 3, 2)        \
+  X(172, 64, 2, 4, 43)          \
+  X(256, 64, 4, 8, 4, 8)        \
+  X(512, 64, 4, 8, 8, 8)        \
+  X(768, 64, 3, 16, 3, 16)      \
+  X(1024, 64, 3, 16, 4, 16)     \
+  X(2048, 128, 3, 16, 8, 16)    \
+  X(3072, 192, 3, 16, 12, 16)   \
+  X(4096, 256, 3, 16, 16, 16)   \
+  X(5120, 320, 4, 16, 20, 16)   \
+  X(6144, 384, 4, 16, 24, 16)   \
+  X(8192, 256, 2, 32, 8, 32)    \
+  X(10000, 512, 2, 20, 25, 20)  \
+  X(11008, 768, 3, 16, 43, 16)  \
+  X(13824, 576, 3, 24, 24, 24)  \
+  X(14336, 512, 2, 32, 14, 32)  \
+  X(16384, 512, 2, 32, 16, 32)
 
 #define X(N, ...) hipError_t launch_n##N(const KArgs& a, int64_t grid, hipStream_t stream);
 KASHIN_SIZES(X)

@@ -2,5 +2,5 @@
 #include "kashin_pair_impl.h"
 
 namespace kashin {
-KASHIN_DEFINE_SIZE(10000, 640, 3, 16, 5, 5, 5, 5)
+KASHIN_DEFINE_SIZE(10000, 512, 2, 20, 25, 20)
 }  // namespace kashin

@@ -2,5 +2,5 @@
 #include "kashin_pair_impl.h"
 
 namespace kashin {
-KASHIN_DEFINE_SIZE(13824, 448, 2, 16, 16, 2, 3, 9)
+KASHIN_DEFINE_SIZE(13824, 576, 3, 24, 24, 24)
 }  // namespace kashin

@@ -2,5 +2,5 @@
 #include "kashin_pair_impl.h"
 
 namespace kashin {
-KASHIN_DEFINE_SIZE(14336, 448, 2, 16, 16, 8, 7)
+KASHIN_DEFINE_SIZE(14336, 512, 2, 32, 14, 32)
 }  // namespace kashin

@@ -2,5 +2,5 @@
 #include "kashin_pair_impl.h"
 
 namespace kashin {
-KASHIN_DEFINE_SIZE(16384, 1024, 4, 16, 8, 8, 16)
+KASHIN_DEFINE_SIZE(16384, 512, 2, 32, 16, 32)
 }  // namespace kashin

@@ -2,5 +2,5 @@
 #include "kashin_pair_impl.h"
 
 namespace kashin {
-KASHIN_DEFINE_SIZE(5120, 320, 3, 16, 16, 4, 5)
+KASHIN_DEFINE_SIZE(5120, 320, 4, 16, 20, 16)
 }  // namespace kashin

@@ -2,5 +2,5 @@
 #include "kashin_pair_impl.h"
 
 namespace kashin {
-KASHIN_DEFINE_SIZE(6144, 384, 3, 16, 16, 8, 3)
+KASHIN_DEFINE_SIZE(6144, 384, 4, 16, 24, 16)
 }  // namespace kashin

@@ -59,40 +59,53 @@ constexpr int bitrev(int x, int bits) {
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
 
-// cos / sin (2 pi m / 16) in double, for compile-time constants
-struct W16 {
-  static constexpr double C1 = 0.92387953251128674;  // cos(pi / 8)
-  static constexpr double S1 = 0.38268343236508978;  // sin(pi / 8)
-  static constexpr double H = 0.70710678118654752;   // sqrt(1 / 2)
-  static constexpr double c[16] = {1, C1, H, S1, 0, -S1, -H, -C1, -1, -C1, -H, -S1, 0, S1, H, C1};
-  static constexpr double s[16] = {0, S1, H, C1, 1, C1, H, S1, 0, -S1, -H, -C1, -1, -C1, -H, -S1};
+// cos / sin (2 pi m / 32) in double, for compile-time constants
+struct W32 {
+  static constexpr double c[32] = {
+      1.0, 0.9807852804032304, 0.9238795325112867, 0.8314696123025452,
+      0.7071067811865476, 0.5555702330196023, 0.38268343236508984, 0.19509032201612833,
+      0, -0.1950903220161282, -0.3826834323650897, -0.555570233019602,
+      -0.7071067811865475, -0.8314696123025453, -0.9238795325112867, -0.9807852804032304,
+      -1.0, -0.9807852804032304, -0.9238795325112868, -0.8314696123025455,
+      -0.7071067811865477, -0.5555702330196022, -0.38268343236509034, -0.19509032201612866,
+      0, 0.1950903220161283, 0.38268343236509, 0.5555702330196018,
+      0.7071067811865474, 0.8314696123025452, 0.9238795325112865, 0.9807852804032303};
+  static constexpr double s[32] = {
+      0, 0.19509032201612825, 0.3826834323650898, 0.5555702330196022,
+      0.7071067811865475, 0.8314696123025452, 0.9238795325112867, 0.9807852804032304,
+      1.0, 0.9807852804032304, 0.9238795325112867, 0.8314696123025455,
+      0.7071067811865476, 0.5555702330196022, 0.3826834323650899, 0.1950903220161286,
+      0, -0.19509032201612836, -0.38268343236508967, -0.555570233019602,
+      -0.7071067811865475, -0.8314696123025452, -0.9238795325112865, -0.9807852804032303,
+      -1.0, -0.9807852804032304, -0.9238795325112866, -0.8314696123025455,
+      -0.7071067811865477, -0.5555702330196022, -0.3826834323650904, -0.19509032201612872};
 };
 constexpr double cabs_d(double v) { return v < 0 ? -v : v; }
 
-// Radix-2 butterfly with a compile-time twiddle w = w16^K (forward, w16 = exp(-2 pi i / 16);
-// the inverse uses w16^-K): (x, y) <- (x + w y, x - w y).  A general twiddle is applied as
+// Radix-2 butterfly with a compile-time twiddle w = w32^K (forward, w32 = exp(-2 pi i / 32);
+// the inverse uses w32^-K): (x, y) <- (x + w y, x - w y).  A general twiddle is applied as
 // w y = m p with p = (w / m) y, m whichever of Re w, Im w is larger in magnitude: p takes
 // two FMAs with the ratio t = Im w / Re w or Re w / Im w (|t| <= 1), and x +- m p four more,
 // six instructions instead of a complex product followed by four additions.
 template <int K, bool INV>
 __device__ __forceinline__ void bfly(float2& x, float2& y) {
-  constexpr int k = K & 15;
+  constexpr int k = K & 31;
   const float2 a = x;
   if constexpr (k == 0) {
     x = cadd(a, y);
     y = csub(a, y);
-  } else if constexpr (k == 8) {
+  } else if constexpr (k == 16) {
     x = csub(a, y);
     y = cadd(a, y);
-  } else if constexpr (k == 4 || k == 12) {
+  } else if constexpr (k == 8 || k == 24) {
     // w = (0, wi), wi = +-1: w y = (-wi y.y, wi y.x)
-    constexpr float wi = static_cast<float>(INV ? W16::s[k] : -W16::s[k]);
+    constexpr float wi = static_cast<float>(INV ? W32::s[k] : -W32::s[k]);
     const float2 wy = make_float2(-wi * y.y, wi * y.x);
     x = cadd(a, wy);
     y = csub(a, wy);
   } else {
-    constexpr double wr = W16::c[k];
-    constexpr double wi = INV ? W16::s[k] : -W16::s[k];
+    constexpr double wr = W32::c[k];
+    constexpr double wi = INV ? W32::s[k] : -W32::s[k];
     float2 p;
     float m;
     if constexpr (cabs_d(wr) >= cabs_d(wi)) {
@@ -109,7 +122,7 @@ __device__ __forceinline__ void bfly(float2& x, float2& y) {
   }
 }
 
-// In-register DFT of a power-of-two length R <= 16: radix-2 decimation in time on the
+// In-register DFT of a power-of-two length R <= 32: radix-2 decimation in time on the
 // bit-reversed input (a compile-time renaming), so every twiddle multiplies the second
 // operand of a butterfly and fuses with it; output in natural order.
 template <int R, bool INV>
@@ -123,7 +136,7 @@ __device__ __forceinline__ void dft_pow2(float2 (&a)[R]) {
     sfor<0, R / len>([&](auto bv) {
       sfor<0, half>([&](auto jv) {
         constexpr int i0 = decltype(bv)::value * len + decltype(jv)::value;
-        bfly<decltype(jv)::value * (16 / len), INV>(b[i0], b[i0 + half]);
+        bfly<decltype(jv)::value * (32 / len), INV>(b[i0], b[i0 + half]);
       });
     });
   });
@@ -161,7 +174,7 @@ __device__ __forceinline__ void dft_pow2_tw(float2 (&a)[R], TW&& tw) {
     sfor<0, R / len>([&](auto bv) {
       sfor<0, half>([&](auto jv) {
         constexpr int i0 = decltype(bv)::value * len + decltype(jv)::value;
-        bfly<decltype(jv)::value * (16 / len), INV>(b[i0], b[i0 + half]);
+        bfly<decltype(jv)::value * (32 / len), INV>(b[i0], b[i0 + half]);
       });
     });
   });
@@ -213,58 +226,80 @@ __device__ __forceinline__ void dft_odd(float2 (&a)[R], Pre&& pre, Sink&& sink) 
   sink(0, sum);
 }
 
-// In-register DFT of an even length R that is not a power of two, from its definition like
-// dft_odd: inputs j and R-j (1 <= j < R/2) are paired into sums and differences, a[0] and
-// a[R/2] enter every output with the signs (+, (-1)^q), and only nonzero constants multiply.
-template <int R, bool INV, class Pre, class Sink>
-__device__ __forceinline__ void dft_even(float2 (&a)[R], Pre&& pre, Sink&& sink) {
-  constexpr int M = R / 2;
-  sfor<1, M>([&](auto jv) {
-    constexpr int j = decltype(jv)::value;
-    const float2 p = pre(j, a[j]), m = pre(R - j, a[R - j]);
-    a[j] = cadd(p, m);
-    a[R - j] = csub(p, m);
-  });
-  const float2 x0 = a[0], xm = pre(M, a[M]);
-  float2 sum = cadd(x0, xm), alt = (M % 2) ? csub(x0, xm) : cadd(x0, xm);  // outputs 0 and M
-  sfor<1, M>([&](auto jv) {
-    constexpr int j = decltype(jv)::value;
-    sum = cadd(sum, a[j]);
-    alt = (j % 2) ? csub(alt, a[j]) : cadd(alt, a[j]);
-  });
-  sfor<1, M>([&](auto qv) {
-    constexpr int q = decltype(qv)::value;
-    float2 re = (q % 2) ? csub(x0, xm) : cadd(x0, xm);
-    float2 im = make_float2(0.f, 0.f);
-    sfor<1, M>([&](auto jv) {
-      constexpr int j = decltype(jv)::value;
-      constexpr int m = (j * q) % R;
-      constexpr float c = CisTab<R>::c[m];
-      constexpr float sn = CisTab<R>::s[m];
-      if constexpr (c != 0.f) {
-        re.x = fmaf(a[j].x, c, re.x);
-        re.y = fmaf(a[j].y, c, re.y);
-      }
-      if constexpr (sn != 0.f) {
-        im.x = fmaf(a[R - j].x, sn, im.x);
-        im.y = fmaf(a[R - j].y, sn, im.y);
-      }
-    });
-    // forward: A_q = re - i im, A_{R-q} = re + i im; inverse swaps them
-    const float2 minus = make_float2(re.x + im.y, re.y - im.x);
-    const float2 plus = make_float2(re.x - im.y, re.y + im.x);
-    sink(q, INV ? plus : minus);
-    sink(R - q, INV ? minus : plus);
-  });
-  sink(0, sum);
-  sink(M, alt);
+// The largest power of two that divides R.
+constexpr int pow2_part(int r) { return r & -r; }
+// k in [0, a b) with k mod a = ka and k mod b = kb (a, b coprime)
+constexpr int crt(int a, int b, int ka, int kb) {
+  int k = ka;
+  while (k % b != kb) k += a;
+  return k;
 }
 
-// DFT of a length R that is not a power of two, outputs handed to sink(q, A_q)
-template <int R, bool INV, class Pre, class Sink>
-__device__ __forceinline__ void dft_small(float2 (&a)[R], Pre&& pre, Sink&& sink) {
-  if constexpr (R % 2 == 1) dft_odd<R, INV>(a, pre, sink);
-  else dft_even<R, INV>(a, pre, sink);
+// In-register DFT of length R = 2^a b, b odd: the prime-factor (Good-Thomas) split into b DFTs of
+// length 2^a and 2^a of length b, whose index maps are compile-time renamings and which needs no
+// twiddles between its two halves; R = 25 as 5 x 5 with them.
+template <int R, bool INV>
+__device__ __forceinline__ void dft_inplace(float2 (&a)[R]) {
+  constexpr int N1 = pow2_part(R), N2 = R / N1;
+  if constexpr (R == 25) {
+    float2 c[25];
+    sfor<0, 5>([&](auto nv) {
+      constexpr int n2 = decltype(nv)::value;
+      float2 b[5];
+      sfor<0, 5>([&](auto iv) { b[decltype(iv)::value] = a[5 * decltype(iv)::value + n2]; });
+      float2 o[5];
+      dft_odd<5, INV>(b, [](int, float2 v) { return v; }, [&](int q, float2 v) { o[q] = v; });
+      sfor<0, 5>([&](auto kv) {
+        constexpr int k1 = decltype(kv)::value;
+        constexpr float wr = CisTab<25>::c[n2 * k1], wi = INV ? CisTab<25>::s[n2 * k1] : -CisTab<25>::s[n2 * k1];
+        const float2 v = o[k1];
+        c[k1 * 5 + n2] = (n2 == 0 || k1 == 0) ? v : make_float2(v.x * wr - v.y * wi, v.x * wi + v.y * wr);
+      });
+    });
+    sfor<0, 5>([&](auto kv) {
+      constexpr int k1 = decltype(kv)::value;
+      float2 b[5];
+      sfor<0, 5>([&](auto iv) { b[decltype(iv)::value] = c[k1 * 5 + decltype(iv)::value]; });
+      dft_odd<5, INV>(b, [](int, float2 v) { return v; }, [&](int q, float2 v) { a[k1 + 5 * q] = v; });
+    });
+  } else if constexpr (N2 == 1) {
+    dft_pow2<R, INV>(a);
+  } else {
+    float2 c[R];
+    sfor<0, N2>([&](auto nv) {
+      constexpr int n2 = decltype(nv)::value;
+      float2 b[N1];
+      sfor<0, N1>([&](auto iv) { b[decltype(iv)::value] = a[(N2 * decltype(iv)::value + N1 * n2) % R]; });
+      if constexpr (N1 > 1) dft_pow2<N1, INV>(b);
+      sfor<0, N1>([&](auto kv) { c[decltype(kv)::value * N2 + n2] = b[decltype(kv)::value]; });
+    });
+    sfor<0, N1>([&](auto kv) {
+      constexpr int k1 = decltype(kv)::value;
+      float2 b[N2];
+      sfor<0, N2>([&](auto iv) { b[decltype(iv)::value] = c[k1 * N2 + decltype(iv)::value]; });
+      dft_odd<N2, INV>(b, [](int, float2 v) { return v; }, [&](int q, float2 v) { a[crt(N1, N2, k1, q)] = v; });
+    });
+  }
+}
+
+template <bool INV>
+__device__ __forceinline__ float2 twmul(float2 v, float2 t) {
+  if constexpr (!INV) return make_float2(v.x * t.x - v.y * t.y, v.x * t.y + v.y * t.x);
+  else return make_float2(v.x * t.x + v.y * t.y, v.y * t.x - v.x * t.y);
+}
+
+// In-register DFT of the twiddled inputs a_r tw(r) (tw(0) = 1; conjugated twiddles on the inverse)
+template <int R, bool INV, class TW>
+__device__ __forceinline__ void dft_tw(float2 (&a)[R], TW&& tw) {
+  if constexpr ((R & (R - 1)) == 0) {
+    dft_pow2_tw<R, INV>(a, tw);
+  } else {
+    sfor<1, R>([&](auto rv) {
+      constexpr int r = decltype(rv)::value;
+      a[r] = twmul<INV>(a[r], tw(rv));
+    });
+    dft_inplace<R, INV>(a);
+  }
 }
 
 // DFT of a[] handed to sink(q, A_q) for every q (power-of-two R: computed in place first).
@@ -297,11 +332,14 @@ struct Cfg {
   static constexpr int B0 = (NB0 + T - 1) / T;
   static constexpr int E = B0 * R0;
   static constexpr int NW = (T + 63) / 64;
-  static constexpr bool WIDE = uniform_resident(N_, T_, NP, rad);
-  static constexpr int PS = pad_shift(N_, WIDE);  // LDS padding: PW spare slots per PG elements
-  static constexpr int PW = pad_width(WIDE);
+  static constexpr int PS = pad_shift(N_);  // generic path: a spare LDS slot per 2^PS elements
   static constexpr int PG = 1 << PS;
-  static constexpr int LDS = N + PW * (N >> PS) + 4;
+  // three-pass path (N = R0 M R0, one butterfly of the outer passes per thread)
+  static constexpr bool RES = NP == 3 && rad[0] == rad[NP - 1] && R0 % 2 == 0 && B0 == 1;
+  static constexpr int M = RES ? rad[1] : 1;
+  static constexpr int S1 = NB0 + (R0 == 8 ? 4 : 2);   // row strides of the two exchange layouts (below)
+  static constexpr int S2 = NB0 + (R0 == 20 ? 8 : 1);
+  static constexpr int LDS = RES ? R0 * (S1 > S2 ? S1 : S2) + 2 : N + (N >> PS) + 4;
 };
 
 template <class C>
@@ -317,12 +355,12 @@ constexpr int ns_inv(int p) {
   return s;
 }
 
-// LDS layout: element k of the length-N complex vector lives at float2 slot pad<C>(k) (C::PW
-// spare slots per C::PG elements, so that both contiguous and stride-16 accesses of a Stockham
+// Generic path's LDS layout: element k of the length-N complex vector lives at float2 slot pad<C>(k)
+// (a spare slot per C::PG elements, so that both contiguous and stride-16 accesses of a Stockham
 // pass spread over the banks).  pad<C>(x + y) = pad<C>(x) + pad<C>(y) whenever x mod PG +
 // y mod PG < PG: a base slot plus compile-time offsets addresses a butterfly's elements.
 template <class C>
-__host__ __device__ constexpr int pad(int i) { return i + C::PW * (i >> C::PS); }
+__host__ __device__ constexpr int pad(int i) { return i + (i >> C::PS); }
 // Whether a Stockham write (element q of butterfly j to b + q S, b = (j / S) S R + j mod S,
 // q < R) can address slots as pad(b) + pad(q S): S a multiple of PG, or S dividing PG with
 // S R a multiple or a divisor of PG (then b mod PG + q S mod PG < PG for every q).
@@ -338,26 +376,6 @@ __device__ __forceinline__ int opaque(int v) {
   asm volatile("" : "+v"(v));
   return v;
 }
-
-// Butterfly index of thread l.  With two spare slots per 32 elements the resident transform
-// gives the butterflies of each 16-lane group to its lanes in the order 0, 2, .., 14, 1, 3, ..,
-// 15: the first pass then writes its outputs 16t + q, q < 16, as 16-byte pairs, and the eight
-// lanes of such a write (butterflies of one parity) cover 32 distinct banks.  Every other
-// access of the transform touches the same 16- and 32-lane index sets as in lane order.
-template <class C>
-constexpr bool lane_perm() {
-  return C::WIDE;
-}
-template <class C>
-__device__ __forceinline__ int bfly(int l) {
-  if constexpr (lane_perm<C>()) {
-    const int m = opaque(l);  // recomputed at each use rather than kept live (or spilled) across the kernel
-    return (m & ~15) | (2 * (m & 7)) | ((m >> 3) & 1);
-  } else {
-    return l;
-  }
-}
-
 
 // Position m of the even/odd order -> index in the row.
 template <int N>
@@ -526,7 +544,7 @@ __device__ __forceinline__ void fft_pass(float2 (&z)[C::E], float2* __restrict__
   constexpr bool FULL = (NB % T) == 0;
   static_assert(SRC != SRC_REGS || (R == C::R0 && NS == 1), "register source must be the first pass");
   static_assert(DST != DST_REGS || (R == C::R0 && NS == N / C::R0), "register target must be the last pass");
-  const int tid = opaque(bfly<C>(threadIdx.x));
+  const int tid = opaque(threadIdx.x);
   float2 a[BP][R];
   sfor<0, BP>([&](auto iv) {
     constexpr int i = decltype(iv)::value;
@@ -629,88 +647,57 @@ __device__ __forceinline__ void apply_P(float2 (&z)[C::E], float2* lds, const fl
   inv_passes<C, 0>(z, lds, tw, mid);
 }
 
-// ------------------------------------------------------------------ resident-table path
-// Launch shapes whose passes all use one power-of-two radix R <= 16 with exactly one
-// butterfly per thread (T == N/R, N/R a multiple of 16) keep the operator's constants out
-// of memory inside the block loop: the twiddles of the last pass (stride N/R, one row
-// of R per thread) and the eps factors of the middle step live in registers, loaded once;
-// the smaller twiddle tables of the inner passes are copied to LDS once.  The forward
-// last pass, the eps step and the inverse first pass are fused: thread t holds Y_k for
-// k = t + q N/R after the forward FFT and needs exactly those elements for the inverse
-// one, plus Y_{N-k}, which thread N/R - t holds; one LDS exchange brings the partner's
-// values, and the element to use is chosen by the factor itself (f_k.y == 0 exactly when
-// eps_k == eps_{N-k}).
-// An inner pass of odd radix R > R0 whose N/R butterflies are each shared by S = T / (N/R)
-// threads (wave-uniform sub-groups; see split_pass).  Its stride must be R0 so that the
-// forward/inverse first passes can apply its twiddles to their outputs.
+// ------------------------------------------------------------------ three-pass resident path
+// N = R0 M R0 with one butterfly of the two outer passes per thread (C::RES): the transform of
+// every length from 256 up.  The operator's constants stay out of memory inside the block loop: the
+// twiddles of the last pass (a row of R0 per thread, kept as a few powers) and the eps factors of the
+// middle step live in registers, loaded once; the inner pass's twiddles are copied to LDS once.  The
+// forward last pass, the eps step and the inverse first pass are fused: thread t holds Y_k for
+// k = t + q N/R0 after the forward FFT and needs exactly those elements for the inverse one, plus
+// Y_{N-k}, which thread N/R0 - t holds; one LDS exchange brings the partner's values.  The inverse
+// runs the same radices in the same order, so it shares every table, conjugated.
+//
+// Three passes because the exchanges through LDS bound the transform together with the VALU: a
+// 64-lane 8-byte write costs the CU 6.5 clocks, an 8-byte read 4, and a 16-byte read, measured at
+// twice the bytes per clock, 4.4, against about 190 two-clock instructions of a radix-16 butterfly
+// over four SIMDs.  One larger inner radix (M = 20, 24, 25, 32) beats two small ones even where
+// some waves idle in it.  Each exchange has a layout of its own, in which every access is free of
+// bank conflicts (8-byte reads resolve per 32 lanes over 64 banks, 8-byte writes per 16 lanes over
+// 32) except a few for R0 = 20 and 24:
+//   first -> inner   element i = R0 t + q (output q of butterfly t) at slot q S1 + t: written in
+//                    lane order; butterfly (jh, jm) of the inner pass reads input r at
+//                    jm S1 + jh + r R0, its lanes running over jm and the low bit of jh
+//   inner -> last    element jh N/R0 + c at the slot of row pair jh >> 1, column c, half jh & 1:
+//                    2 ((jh >> 1) S2 + c) + (jh & 1), so that the last pass (input r of butterfly t =
+//                    row r, column t) reads two rows in 16 bytes; the partner exchange reuses it
+//                    (8-byte reads throughout instead cost N = 4096 5 %)
+// N = 5120 as 16 x 20 x 16 against the four-pass 16 x 16 x 4 x 5 with its tables in memory: see
+// the launch shapes in kashin_dispatch.hip for the measured times.
+//
+// A radix M > 32 is split: its R0^2 butterflies are each shared by S = T / R0^2 threads
+// (wave-uniform sub-groups; see split_pass), its twiddles applied by the first pass to its outputs.
 template <class C>
-constexpr bool is_split_pass(int p) {
-  const int R = C::rad[p];
-  return C::NP == 3 && p == 1 && R % 2 == 1 && R > C::R0 && (C::N / R) % 64 == 0 && C::T % (C::N / R) == 0 &&
-         C::T / (C::N / R) <= (R - 1) / 2;
+constexpr bool resident_ok() {
+  return C::RES;
 }
 template <class C>
 constexpr bool has_split_pass() {
-  return C::NP == 3 && is_split_pass<C>(1);
+  return C::RES && C::M > 32;
 }
-// An inner pass of a radix R < R0 that is not a power of two (odd, or 12) between two radix-R0
-// passes (N = R0 R R0): its N/R butterflies spread evenly over the T >= N/R0 threads, each read
-// once and transformed by one thread with its twiddles applied to the inputs.
-template <class C>
-constexpr bool is_small_inner_pass(int p) {
-  const int R = C::rad[p];
-  return C::NP == 3 && p == 1 && (R & (R - 1)) != 0 && (R % 2 == 1 || R == 12) && R < C::R0 && C::T % 64 == 0 &&
-         (C::N / R) % C::T == 0;
-}
-// Resident shapes: first and last radix R0 (a power of two <= 16), one butterfly of those passes
-// per thread, and either a split inner pass or inner radices that are powers of two dividing R0
-// in a palindromic sequence (so that the inverse transform meets the same radices and strides,
-// and reuses the forward twiddle tables conjugated); an inner pass of radix R gives each thread
-// R0 / R butterflies.
-template <class C>
-constexpr bool resident_ok() {
-  constexpr int R0 = C::R0;
-  if (!(C::NP >= 2 && R0 <= 16 && (R0 & (R0 - 1)) == 0 && C::rad[C::NP - 1] == R0 && (C::N / R0) % C::PG == 0))
-    return false;
-  if (has_split_pass<C>()) return C::T >= C::N / R0;
-  if (is_small_inner_pass<C>(1)) return C::T >= C::N / R0 && (C::N / C::rad[1]) % C::PG == 0;
-  for (int p = 0; p < C::NP; ++p) {
-    const int r = C::rad[p];
-    if (r < 2 || (r & (r - 1)) != 0 || R0 % r != 0 || r != C::rad[C::NP - 1 - p]) return false;
-    if ((C::N / r) % C::PG != 0) return false;
-  }
-  return C::T == C::N / R0;
-}
-// LDS slots (float2) of the inner-pass twiddle tables (passes 1 .. NP-2), after the FFT buffer
-template <class C>
-constexpr int small_tw_offset(int p) {
-  int off = 0;
-  for (int q = 1; q < p; ++q) off += ns_fwd<C>(q) * C::rad[q];
-  return off;
-}
-// LDS after the FFT buffer on the resident path: the inner-pass twiddle tables, then (with a
-// split pass) the 256-byte lane order of its butterflies
+// LDS slots of the inner pass's twiddle table, after the exchange buffer
 template <class C>
 constexpr int small_tw_total() {
-  return resident_ok<C>() ? small_tw_offset<C>(C::NP - 1) + (has_split_pass<C>() ? 32 : 0) : 0;
+  return C::RES ? C::R0 * ((C::M + 1) & ~1) : 0;
 }
 
-// eps factors f_k of the fused step for the thread's elements k = t + q N/R: kept as R complex
-// values, or -- COMPACT, for kernels whose block loop is register-bound on the split shape (which
-// also keep only powers 1 and 4 of the last-pass twiddle, see stored_tw) -- as
-// e^{i pi t/N}/N and a mask (bit 2q: eps_k < 0, bit 2q + 1: eps_k != eps_{N-k}), from which
-// f_k = eps_k / N or eps_k e^{i pi k/N} / N = eps_k (e^{i pi t/N} / N) e^{i pi q/R} is rebuilt at
-// each use.
+// eps factors f_k of the fused step for the thread's elements k = t + q N/R0: kept as R0 complex
+// values, or -- COMPACT, for kernels whose block loop is register-bound (the split shape, radices
+// above 16, a 128-register budget) -- as e^{i pi t/N}/N and two masks (bit q: eps_k < 0, and
+// eps_k != eps_{N-k}), from which f_k = eps_k / N or eps_k e^{i pi k/N} / N =
+// eps_k (e^{i pi t/N} / N) e^{i pi q/R0} is rebuilt at each use.
 template <class C>
 constexpr bool compact_eps() {
-  return has_split_pass<C>() || (C::W >= 4 && C::R0 == 16);  // split shape, or a 128-register budget
-}
-// vhat of the quantizer's block loop kept in private memory between its steps (16-byte loads and
-// stores of the whole array around the two vhat-steps of a block) rather than in registers, where
-// the 128-register budget would otherwise spill it value by value inside the transforms
-template <class C>
-constexpr bool vh_in_memory() {
-  return !has_split_pass<C>() && C::W >= 4 && C::R0 == 16 && C::E % 2 == 0;
+  return has_split_pass<C>() || C::R0 > 16 || (C::W >= 4 && C::R0 == 16);
 }
 template <class C, bool COMPACT>
 struct EpsRegs {
@@ -719,27 +706,15 @@ struct EpsRegs {
 template <class C>
 struct EpsRegs<C, true> {
   float2 base;
-  uint32_t bits;
-};
-// e^{i pi q / 16}
-struct Half32 {
-  static constexpr double c[16] = {1.0, 0.9807852804032304, 0.9238795325112867, 0.8314696123025452,
-                                   0.7071067811865476, 0.5555702330196023, 0.38268343236508984, 0.19509032201612833,
-                                   0.0, -0.1950903220161282, -0.3826834323650897, -0.555570233019602,
-                                   -0.7071067811865475, -0.8314696123025453, -0.9238795325112867, -0.9807852804032304};
-  static constexpr double s[16] = {0.0, 0.19509032201612825, 0.3826834323650898, 0.5555702330196022,
-                                   0.7071067811865475, 0.8314696123025452, 0.9238795325112867, 0.9807852804032304,
-                                   1.0, 0.9807852804032304, 0.9238795325112867, 0.8314696123025455,
-                                   0.7071067811865476, 0.5555702330196022, 0.3826834323650899, 0.1950903220161286};
+  uint32_t neg, swap;
 };
 // f_k for element q, and whether it takes the partner value (eps_k != eps_{N-k})
 template <class C, int q, bool COMPACT>
 __device__ __forceinline__ float2 eps_factor(const EpsRegs<C, COMPACT>& e, bool& partner) {
   if constexpr (COMPACT) {
-    static_assert(C::R0 == 16, "compact eps factors assume radix 16");
-    partner = (e.bits >> (2 * q + 1)) & 1u;
-    const bool neg = (e.bits >> (2 * q)) & 1u;
-    constexpr float cx = static_cast<float>(Half32::c[q]), cy = static_cast<float>(Half32::s[q]);
+    partner = (e.swap >> q) & 1u;
+    const bool neg = (e.neg >> q) & 1u;
+    constexpr float cx = HalfTab<C::R0>::c[q], cy = HalfTab<C::R0>::s[q];
     constexpr float inv_n = static_cast<float>(1.0 / C::N);
     const float2 g = partner ? make_float2(e.base.x * cx - e.base.y * cy, e.base.x * cy + e.base.y * cx)
                              : make_float2(inv_n, 0.f);
@@ -753,82 +728,76 @@ __device__ __forceinline__ float2 eps_factor(const EpsRegs<C, COMPACT>& e, bool&
 
 template <class C, bool COMPACT = false>
 struct ResRegs {
-  static constexpr bool compact = COMPACT;
-  float2 tw[C::R0];         // w_N^(r t) for r in {1, 2, 3, 4, 8, 12}: the rest are products of two of these
-  EpsRegs<C, COMPACT> eps;  // eps factors of the fused step for elements k = t + r N/R
+  static constexpr bool compact = COMPACT && C::R0 == 16;
+  float2 tw[C::R0];         // stored powers of w_N^t (kept_tw); the rest are products of two of these
+  EpsRegs<C, COMPACT> eps;  // eps factors of the fused step for elements k = t + r N/R0
 };
 
-// twiddle r of the last pass from the stored powers (R = 16: r = 4a + b, w_r = w_4a * w_b)
 __device__ __forceinline__ float2 cmulf(float2 x, float2 y) {
   return make_float2(x.x * y.x - x.y * y.y, x.x * y.y + x.y * y.x);
 }
-// stored power r of w_N^t: all six kept, or (compact) only r = 1 and 4 with 2, 3, 8, 12 derived
-template <class C, int r, class RR>
-__device__ __forceinline__ float2 stored_tw(const RR& rr) {
-  if constexpr (!RR::compact || r == 1 || r == 4) return rr.tw[r];
-  else if constexpr (r == 2) return cmulf(rr.tw[1], rr.tw[1]);
-  else if constexpr (r == 3) return cmulf(stored_tw<C, 2>(rr), rr.tw[1]);
-  else if constexpr (r == 8) return cmulf(rr.tw[4], rr.tw[4]);
-  else return cmulf(stored_tw<C, 8>(rr), rr.tw[4]);  // r == 12
+// Twiddle r of the last pass, w_N^{r t}: below radix 16 all are kept; else r = 4a + b is the product
+// w_{4a} w_b (one rounding) of the kept powers 1, 2, 3, 4, 8, 12, ..; compact keeps only 1 and 4.
+template <class C, class RR>
+constexpr bool kept_tw(int r) {
+  return C::R0 < 16 ? r > 0 : (RR::compact ? (r == 1 || r == 4) : r > 0 && (r < 4 || r % 4 == 0));
 }
 template <class C, int r, class RR>
 __device__ __forceinline__ float2 last_tw(const RR& rr) {
-  if constexpr (C::R0 < 16 || r <= 4 || r == 8 || r == 12) {
-    return stored_tw<C, r>(rr);
-  } else {
-    constexpr int hi = r & ~3, lo = r & 3;
-    return cmulf(stored_tw<C, hi>(rr), stored_tw<C, lo>(rr));
-  }
+  if constexpr (kept_tw<C, RR>(r)) return rr.tw[r];
+  else if constexpr (r == 2) return cmulf(rr.tw[1], rr.tw[1]);
+  else if constexpr (r == 3) return cmulf(last_tw<C, 2>(rr), rr.tw[1]);
+  else if constexpr (r % 4 == 0) return cmulf(last_tw<C, r - 4>(rr), rr.tw[4]);
+  else return cmulf(last_tw<C, (r & ~3)>(rr), last_tw<C, (r & 3)>(rr));
 }
+
+__device__ __forceinline__ void launder(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
 
 // Before each last pass: declare the stored powers modified (in place, no instruction), so
 // the products formed from them are neither hoisted out of the block loop nor shared between
-// the two last passes of one application of P, either of which would keep nine more complex
+// the two last passes of one application of P, either of which would keep many more complex
 // values live.
 template <class C, class RR>
 __device__ __forceinline__ void launder_powers(RR& rr) {
-  if constexpr (C::R0 == 16) {
-    if constexpr (RR::compact)
-      asm volatile("" : "+v"(rr.tw[1].x), "+v"(rr.tw[1].y), "+v"(rr.tw[4].x), "+v"(rr.tw[4].y));
-    else
-      asm volatile(""
-                   : "+v"(rr.tw[1].x), "+v"(rr.tw[1].y), "+v"(rr.tw[2].x), "+v"(rr.tw[2].y), "+v"(rr.tw[3].x),
-                     "+v"(rr.tw[3].y), "+v"(rr.tw[4].x), "+v"(rr.tw[4].y), "+v"(rr.tw[8].x), "+v"(rr.tw[8].y),
-                     "+v"(rr.tw[12].x), "+v"(rr.tw[12].y));
+  if constexpr (C::R0 >= 16) {
+    sfor<1, C::R0>([&](auto rv) {
+      constexpr int r = decltype(rv)::value;
+      if constexpr (kept_tw<C, RR>(r)) launder(rr.tw[r]);
+    });
   }
-  // the compact eps factors are rebuilt inside the block loop, not hoisted out of it as R live values
-  if constexpr (RR::compact) asm volatile("" : "+v"(rr.eps.base.x), "+v"(rr.eps.base.y), "+v"(rr.eps.bits));
+  // the compact eps factors are rebuilt inside the block loop, not hoisted out of it as R0 live values
+  if constexpr (compact_eps<C>() && std::is_same<decltype(rr.eps), EpsRegs<C, true>>::value)
+    asm volatile("" : "+v"(rr.eps.base.x), "+v"(rr.eps.base.y), "+v"(rr.eps.neg), "+v"(rr.eps.swap));
 }
 
 template <class C, class RR>
 __device__ __forceinline__ void resident_load(RR& rr, float2* lds, const float2* __restrict__ tw,
                                               const float4* __restrict__ mid) {
   constexpr int R = C::R0;
-  constexpr int NB = C::N / R;
-  const int t = bfly<C>(threadIdx.x);
+  constexpr int NB = C::NB0;
+  const int t = threadIdx.x;
   const int tl = (C::T == NB || t < NB) ? t : 0;  // threads past the last butterfly load row 0 (unused)
-  const float4* t4 = reinterpret_cast<const float4*>(tw + tw_offset<C, false>(C::NP - 1) + tl * R);
+  const float4* t4 = reinterpret_cast<const float4*>(tw + tw_offset<C, false>(2) + tl * R);
   sfor<0, R / 2>([&](auto hv) {
     constexpr int h = decltype(hv)::value;
-    constexpr bool keep0 = (R < 16) || (2 * h <= 4 || 2 * h == 8 || 2 * h == 12);
-    constexpr bool keep1 = (R < 16) || (2 * h + 1 <= 4);
-    if constexpr (keep0 || keep1) {
+    if constexpr (kept_tw<C, RR>(2 * h) || kept_tw<C, RR>(2 * h + 1)) {
       const float4 q = t4[h];
-      if constexpr (keep0) rr.tw[2 * h] = make_float2(q.x, q.y);
-      if constexpr (keep1) rr.tw[2 * h + 1] = make_float2(q.z, q.w);
+      rr.tw[2 * h] = make_float2(q.x, q.y);
+      rr.tw[2 * h + 1] = make_float2(q.z, q.w);
     }
   });
-  if constexpr (RR::compact) {
-    uint32_t bits = 0;
+  if constexpr (std::is_same<decltype(rr.eps), EpsRegs<C, true>>::value) {
+    uint32_t neg = 0, swap = 0;
     sfor<0, R>([&](auto rv) {
       constexpr int q = decltype(rv)::value;
       const float4 m = mid[tl * R + q];  // {Re f_k, Im f_k, -, eps_k}
-      bits |= (m.w < 0.f ? 1u : 0u) << (2 * q);
-      bits |= (m.y != 0.f ? 1u : 0u) << (2 * q + 1);
+      neg |= (m.w < 0.f ? 1u : 0u) << q;
+      swap |= (m.y != 0.f ? 1u : 0u) << q;
     });
     float sn, cs;
     sincospif(static_cast<float>(tl) / static_cast<float>(C::N), &sn, &cs);
-    rr.eps.bits = bits;
+    rr.eps.neg = neg;
+    rr.eps.swap = swap;
     rr.eps.base = make_float2(cs * static_cast<float>(1.0 / C::N), sn * static_cast<float>(1.0 / C::N));
   } else {
     sfor<0, R>([&](auto rv) {
@@ -836,114 +805,90 @@ __device__ __forceinline__ void resident_load(RR& rr, float2* lds, const float2*
       rr.eps.f[decltype(rv)::value] = make_float2(m.x, m.y);
     });
   }
-  // inner-pass tables, transposed so that the lanes of a wave (consecutive jm) read
-  // consecutive LDS words (the [jm][r] rows of the global layout are 8R bytes apart, which
-  // would put every lane of a 16-lane group on the same banks): [r][jm] for a split pass,
-  // else [r / 2][jm] pairs (entries r and r + 1 side by side, one 16-byte read per pair)
+  // inner-pass table, entry [jm][r] of the global layout: [r][jm] for a split pass (the first pass
+  // reads entries jm, jm + 1), else [r / 2][jm] pairs (entries r and r + 1 side by side, one 16-byte
+  // read per pair), the lanes of a wave (consecutive jm) reading consecutive words either way
   float2* small = lds + C::LDS;
-  sfor<1, C::NP - 1>([&](auto pv) {
-    constexpr int P = decltype(pv)::value;
-    constexpr int NS = ns_fwd<C>(P);
-    constexpr int RP = C::rad[P];
-    constexpr int OFF = small_tw_offset<C>(P);
-    for (int i = t; i < NS * RP; i += C::T) {
-      const int jm = i / RP, r = i % RP;
-      if constexpr (is_split_pass<C>(P) || is_small_inner_pass<C>(P))
-        small[OFF + r * NS + jm] = tw[tw_offset<C, false>(P) + i];
-      else small[OFF + 2 * ((r / 2) * NS + jm) + (r & 1)] = tw[tw_offset<C, false>(P) + i];
-    }
-  });
-  if constexpr (has_split_pass<C>()) {
-    const unsigned char* order = SplitOrder<C::rad[1]>::j;
-    unsigned char* dst = reinterpret_cast<unsigned char*>(small + small_tw_offset<C>(C::NP - 1));
-    for (int i = threadIdx.x; i < 256; i += C::T) dst[i] = order[i];
+  for (int i = t; i < R * C::M; i += C::T) {
+    const int jm = i / C::M, r = i % C::M;
+    const int at = has_split_pass<C>() ? r * R + jm : 2 * ((r / 2) * R + jm) + (r & 1);
+    small[at] = tw[tw_offset<C, false>(1) + i];
   }
   __syncthreads();
 }
 
-template <bool INV>
-__device__ __forceinline__ float2 twmul(float2 v, float2 t) {
-  if constexpr (!INV) return make_float2(v.x * t.x - v.y * t.y, v.x * t.y + v.y * t.x);
-  else return make_float2(v.x * t.x + v.y * t.y, v.y * t.x - v.x * t.y);
-}
+// Butterfly (jh, jm) = jh R0 + jm of the inner pass that lane l takes: lanes run over the low bit of
+// jh first, then jm, so that 16 lanes write 16 consecutive slots of the inner -> last layout.
+template <class C>
+struct InnerLane {
+  int rd, wr, jm;
+  __device__ __forceinline__ explicit InnerLane(int l) {
+    const int p = l & 1, hq = (l >> 1) / C::R0;
+    jm = (l >> 1) % C::R0;
+    rd = jm * C::S1 + 2 * hq + p;
+    wr = 2 * (hq * C::S2 + jm) + p;
+  }
+};
 
-// Inner pass p (1 <= p <= NP-2) of the resident path: radix R = rad[p], stride NS = the
-// product of the radices before it, LDS -> LDS, twiddles from the LDS copy of the pass-p table;
-// thread t takes butterflies t + T i, i < R0 / R.
-template <class C, int P, bool INV>
-__device__ __forceinline__ void res_small_pass(float2* __restrict__ lds, int t) {
-  constexpr int R = C::rad[P];
-  constexpr int NB = C::N / R;
-  constexpr int NS = ns_fwd<C>(P);
-  constexpr int BPT = NB / C::T;
-  static_assert(BPT * C::T == NB && NB % C::PG == 0 && pad_offsets_ok<C>(NS, R), "small inner pass shape");
-  float2 a[BPT][R];
+// The inner pass: R0^2 butterflies of radix M, thread t taking t, t + T, ..; LDS -> LDS in place
+// (every read completes before any write).
+template <class C, bool INV>
+__device__ __forceinline__ void res_inner_pass(float2* __restrict__ lds) {
+  const int t = opaque(threadIdx.x);  // each pass forms its own addresses: none stays live across others
+  constexpr int R0 = C::R0;
+  constexpr int M = C::M;
+  constexpr int NB = R0 * R0;
+  constexpr int BPT = (NB + C::T - 1) / C::T;
+  static_assert(C::LDS % 2 == 0, "16-byte twiddle pairs");
+  float2 a[BPT][M];
+  constexpr int MP = (M + 1) / 2;
+  // twiddle pairs read before the barrier, so that their latency passes while the waves gather there
+  constexpr int PF = BPT == 1 ? (MP < 8 ? MP : 8) : 0;
+  float4 pf[PF > 0 ? PF : 1];
   sfor<0, BPT>([&](auto iv) {
     constexpr int i = decltype(iv)::value;
-    const float2* rb = lds + pad<C>(t + C::T * i);
-    sfor<0, R>([&](auto rv) { a[i][decltype(rv)::value] = rb[decltype(rv)::value * pad<C>(NB)]; });
+    const int l = t + C::T * i;
+    if (NB % C::T == 0 || l < NB) {
+      const InnerLane<C> il(l);
+      const float2* rb = lds + il.rd;
+      sfor<0, M>([&](auto rv) { a[i][decltype(rv)::value] = rb[decltype(rv)::value * R0]; });
+      if constexpr (PF > 0) {
+        const float4* tb = reinterpret_cast<const float4*>(lds + C::LDS) + il.jm;
+        sfor<0, PF>([&](auto hv) { pf[decltype(hv)::value] = tb[decltype(hv)::value * R0]; });
+      }
+    }
   });
   __syncthreads();
   sfor<0, BPT>([&](auto iv) {
     constexpr int i = decltype(iv)::value;
-    const int j = t + C::T * i;
-    const int jm = j % NS;
-    const float2* tb = lds + C::LDS + small_tw_offset<C>(P) + jm;  // table [r][jm]
-    auto pre = [&](int r, float2 v) {
-      if (r == 0) return v;
-      const float2 w = tb[r * NS];
-      return INV ? make_float2(v.x * w.x + v.y * w.y, v.y * w.x - v.x * w.y)
-                 : make_float2(v.x * w.x - v.y * w.y, v.x * w.y + v.y * w.x);
-    };
-    float2* wb = lds + pad<C>((j / NS) * NS * R + jm);
-    dft_small<R, INV>(a[i], pre, [&](int q, float2 v) { wb[pad<C>(q * NS)] = v; });
-  });
-  __syncthreads();
-}
-
-template <class C, int P, bool INV>
-__device__ __forceinline__ void res_inner_pass(float2* __restrict__ lds, int t) {
-  constexpr int R = C::rad[P];
-  constexpr int NB = C::N / R;
-  constexpr int NS = ns_fwd<C>(P);
-  constexpr int BPT = NB / C::T;
-  static_assert(BPT * C::T == NB && BPT * R == C::R0, "inner pass butterflies per thread");
-  float2 a[BPT][R];
-  sfor<0, BPT>([&](auto iv) {
-    constexpr int i = decltype(iv)::value;
-    const float2* rb = lds + pad<C>(t + C::T * i);
-    sfor<0, R>([&](auto rv) { a[i][decltype(rv)::value] = rb[decltype(rv)::value * pad<C>(NB)]; });
-  });
-  __syncthreads();
-  static_assert(R % 2 == 0 && small_tw_offset<C>(P) % 2 == 0 && C::LDS % 2 == 0, "16-byte twiddle pairs");
-  static_assert(pad_offsets_ok<C>(NS, R), "inner pass stride");
-  sfor<0, BPT>([&](auto iv) {
-    constexpr int i = decltype(iv)::value;
-    const int j = t + C::T * i;
-    const int jm = j % NS;
-    const float4* tb = reinterpret_cast<const float4*>(lds + C::LDS + small_tw_offset<C>(P)) + jm;  // [r / 2][jm]
-    dft_pow2_tw<R, INV>(a[i], [&](auto rv) {
-      constexpr int r = decltype(rv)::value;
-      const float4 q = tb[(r / 2) * NS];
-      return (r & 1) ? make_float2(q.z, q.w) : make_float2(q.x, q.y);
-    });
-    float2* wb = lds + pad<C>((j / NS) * NS * R + jm);
-    sfor<0, R>([&](auto qv) { wb[pad<C>(decltype(qv)::value * NS)] = a[i][decltype(qv)::value]; });
+    const int l = t + C::T * i;
+    if (NB % C::T == 0 || l < NB) {
+      const InnerLane<C> il(l);
+      const float4* tb = reinterpret_cast<const float4*>(lds + C::LDS) + il.jm;  // [r / 2][jm]
+      dft_tw<M, INV>(a[i], [&](auto rv) {
+        constexpr int r = decltype(rv)::value;
+        float4 q;
+        if constexpr (r / 2 < PF) q = pf[r / 2];
+        else q = tb[(r / 2) * R0];
+        return (r & 1) ? make_float2(q.z, q.w) : make_float2(q.x, q.y);
+      });
+      float2* wb = lds + il.wr;
+      sfor<0, M>([&](auto qv) { wb[decltype(qv)::value * 2 * R0] = a[i][decltype(qv)::value]; });
+    }
   });
   __syncthreads();
 }
 
-// Split inner pass: odd radix R, stride NS = R0, NB = N/R butterflies, each shared by the
-// S = T/NB threads t = j + s NB (s is uniform across a wave).  Every sub-group streams the
-// R inputs of butterfly j from LDS once, forming the pair sums and differences
-// a_r +- a_{R-r}, and accumulates only its own share of the (R-1)/2 output pairs (q, R-q);
-// the twiddles were applied by the pass before.  All sub-groups run one code path: their
-// DFT constants come from a table in constant memory at a wave-uniform address (scalar
-// loads into SGPR operands of the FMAs).
-template <class C, int P>
+// Split inner pass: odd radix R = M, R0^2 butterflies, each shared by S = T / R0^2 threads
+// t = l + s R0^2 (s is uniform across a wave).  Every sub-group streams the R inputs of butterfly l
+// from LDS once, forming the pair sums and differences a_r +- a_{R-r}, and accumulates only its own
+// share of the (R-1)/2 output pairs (q, R-q); the twiddles were applied by the pass before.  All
+// sub-groups run one code path: their DFT constants come from a table in constant memory at a
+// wave-uniform address (scalar loads into SGPR operands of the FMAs).
+template <class C>
 struct SplitShape {
-  static constexpr int R = C::rad[P];
-  static constexpr int NB = C::N / R;
+  static constexpr int R = C::M;
+  static constexpr int NB = C::R0 * C::R0;
   static constexpr int S = C::T / NB;         // threads per butterfly
   static constexpr int H = (R - 1) / 2;       // output pairs (q, R - q)
   static constexpr int QP = (H + S - 1) / S;  // output pairs per sub-group
@@ -976,23 +921,21 @@ constexpr SplitCoef<R, S> make_split_coef() {
 template <int R, int S>
 __constant__ SplitCoef<R, S> split_coef = make_split_coef<R, S>();
 
-template <class C, int P, bool INV>
-__device__ __forceinline__ void split_pass(float2* __restrict__ lds, int t) {
-  using SS = SplitShape<C, P>;
+template <class C, bool INV>
+__device__ __forceinline__ void split_pass(float2* __restrict__ lds) {
+  const int t = opaque(threadIdx.x);
+  using SS = SplitShape<C>;
   constexpr int R = SS::R;
   constexpr int NB = SS::NB;
   constexpr int S = SS::S;
   constexpr int QP = SS::QP;
   constexpr int H = SS::H;
-  constexpr int NS = ns_fwd<C>(P);
-  static_assert(NB % 64 == 0 && NS % C::PG == 0, "split pass strides");
+  constexpr int R0 = C::R0;
+  static_assert(R % 2 == 1 && NB % 64 == 0 && C::T % NB == 0 && S <= H, "split pass shape");
   const int s = __builtin_amdgcn_readfirstlane(t / NB);  // uniform across a wave
-  // butterfly of this lane: the order of SplitOrder (bank-conflict-free reads in seven of the
-  // eight 32-lane halves, conflict-free writes), kept in LDS after the twiddle tables
-  static_assert(NB == 256, "split-pass lane order covers 256 butterflies");
-  const int j = reinterpret_cast<const unsigned char*>(lds + C::LDS + small_tw_offset<C>(C::NP - 1))[t - s * NB];
+  const InnerLane<C> il(t - s * NB);
   const float* __restrict__ cf = split_coef<R, S>.v + s * (H * QP * 2);
-  const float2* rb = lds + pad<C>(j);
+  const float2* rb = lds + il.rd;
   const float2 x0 = rb[0];
   float2 re[QP], im[QP];
   sfor<0, QP>([&](auto iv) {
@@ -1000,168 +943,162 @@ __device__ __forceinline__ void split_pass(float2* __restrict__ lds, int t) {
     im[decltype(iv)::value] = make_float2(0.f, 0.f);
   });
   float2 sum = x0;
-  // Input pairs in chunks of CH, software-pipelined: the LDS reads and constant loads of chunk
-  // c + 1 are issued after an explicit wait for those of chunk c, so that the wait (LDS and
-  // scalar loads share one counter, and scalar loads return out of order) never covers loads
-  // that were just issued; chunk c's FMAs then run while chunk c + 1's loads are in flight.
-  constexpr int CH = 1;
-  constexpr int NCH = (H + CH - 1) / CH;
-  float2 pin[2][CH], mnn[2][CH];
-  float cin[2][CH][2 * QP];
+  // Input pairs, software-pipelined: the LDS reads and constant loads of pair r + 1 are issued after
+  // an explicit wait for those of pair r, so that the wait (LDS and scalar loads share one counter,
+  // and scalar loads return out of order) never covers loads that were just issued; pair r's FMAs
+  // then run while pair r + 1's loads are in flight.
+  float2 pin[2], mnn[2];
+  float cin[2][2 * QP];
   auto fetch = [&](auto cv) {
     constexpr int c = decltype(cv)::value;
-    sfor<0, CH>([&](auto uv) {
-      constexpr int u = decltype(uv)::value;
-      constexpr int r = c * CH + u + 1;
-      if constexpr (r <= H) {
-        pin[c % 2][u] = rb[r * pad<C>(NB)];
-        mnn[c % 2][u] = rb[(R - r) * pad<C>(NB)];
-        sfor<0, 2 * QP>([&](auto ev) { cin[c % 2][u][decltype(ev)::value] = cf[(r - 1) * QP * 2 + decltype(ev)::value]; });
-      }
-    });
+    constexpr int r = c + 1;
+    pin[c % 2] = rb[r * R0];
+    mnn[c % 2] = rb[(R - r) * R0];
+    sfor<0, 2 * QP>([&](auto ev) { cin[c % 2][decltype(ev)::value] = cf[c * QP * 2 + decltype(ev)::value]; });
   };
   fetch(std::integral_constant<int, 0>{});
-  sfor<0, NCH>([&](auto cv) {
+  sfor<0, H>([&](auto cv) {
     constexpr int c = decltype(cv)::value;
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): chunk c's values are in registers
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): pair c's values are in registers
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (c + 1 < NCH) fetch(std::integral_constant<int, c + 1>{});
+    if constexpr (c + 1 < H) fetch(std::integral_constant<int, c + 1>{});
     __builtin_amdgcn_sched_barrier(0);
-    sfor<0, CH>([&](auto uv) {
-      constexpr int u = decltype(uv)::value;
-      if constexpr (c * CH + u + 1 <= H) {
-        const float2 p = pin[c % 2][u], m = mnn[c % 2][u];
-        const float2 sp = cadd(p, m), dm = csub(p, m);
-        sum = cadd(sum, sp);
-        sfor<0, QP>([&](auto iv) {
-          constexpr int i = decltype(iv)::value;
-          const float cc = cin[c % 2][u][2 * i], sn = cin[c % 2][u][2 * i + 1];
-          re[i].x = fmaf(sp.x, cc, re[i].x);
-          re[i].y = fmaf(sp.y, cc, re[i].y);
-          im[i].x = fmaf(dm.x, sn, im[i].x);
-          im[i].y = fmaf(dm.y, sn, im[i].y);
-        });
-      }
+    const float2 p = pin[c % 2], m = mnn[c % 2];
+    const float2 sp = cadd(p, m), dm = csub(p, m);
+    sum = cadd(sum, sp);
+    sfor<0, QP>([&](auto iv) {
+      constexpr int i = decltype(iv)::value;
+      const float cc = cin[c % 2][2 * i], sn = cin[c % 2][2 * i + 1];
+      re[i].x = fmaf(sp.x, cc, re[i].x);
+      re[i].y = fmaf(sp.y, cc, re[i].y);
+      im[i].x = fmaf(dm.x, sn, im[i].x);
+      im[i].y = fmaf(dm.y, sn, im[i].y);
     });
   });
   __syncthreads();
   // forward: A_q = re - i im, A_{R-q} = re + i im; the inverse swaps them
   const int q0 = s * QP + 1;
-  float2* wb = lds + pad<C>((j / NS) * NS * R + (j % NS));
+  float2* wb = lds + il.wr;
   sfor<0, QP>([&](auto iv) {
     constexpr int i = decltype(iv)::value;
     const float2 minus = make_float2(re[i].x + im[i].y, re[i].y - im[i].x);
     const float2 plus = make_float2(re[i].x - im[i].y, re[i].y + im[i].x);
     if (H % QP == 0 || q0 + i <= H) {
-      wb[(q0 + i) * pad<C>(NS)] = INV ? plus : minus;
-      wb[(R - q0 - i) * pad<C>(NS)] = INV ? minus : plus;
+      wb[(q0 + i) * 2 * R0] = INV ? plus : minus;
+      wb[(R - q0 - i) * 2 * R0] = INV ? minus : plus;
     }
   });
   if (s == 0) wb[0] = sum;
   __syncthreads();
 }
 
-template <class C, int P, bool INV>
-__device__ __forceinline__ void res_inner_passes(float2* lds, int t) {
-  if constexpr (P >= 1 && P <= C::NP - 2) {
-    // the radices are palindromic: the inverse FFT meets the same radices and strides as the forward one
-    if constexpr (is_split_pass<C>(P)) split_pass<C, P, INV>(lds, t);
-    else if constexpr (is_small_inner_pass<C>(P)) res_small_pass<C, P, INV>(lds, t);
-    else res_inner_pass<C, P, INV>(lds, t);
-    res_inner_passes<C, P + 1, INV>(lds, t);
-  }
+template <class C, bool INV>
+__device__ __forceinline__ void res_inner(float2* lds) {
+  if constexpr (has_split_pass<C>()) split_pass<C, INV>(lds);
+  else res_inner_pass<C, INV>(lds);
 }
 
-// First pass (stride 1) of either direction: a[] -> LDS, element q to t R + q.  When the
-// next pass is a split pass its input twiddles are applied here, to the outputs: element
-// t R0 + q is input r = t / (NB1 / R0) of a butterfly with j mod R0 = q, so its twiddle is
-// entry [r][q] of the LDS copy of that pass's table.
+// First pass (stride 1) of either direction: a[] -> LDS.  When the inner pass is split its input
+// twiddles are applied here, to the outputs: element t R0 + q is input r = t / R0 of a butterfly
+// with jm = q, so its twiddle is entry [r][q] of the LDS copy of that pass's table.
 template <class C, bool INV>
 __device__ __forceinline__ void res_first_pass(float2 (&a)[C::R0], float2* lds, int t) {
   constexpr int R = C::R0;
-  static_assert(C::PG % R == 0, "first pass: element q of butterfly t at slot pad(t R) + q");
-  float2* wb = lds + pad<C>(t * R);
+  dft_inplace<R, INV>(a);
   if constexpr (has_split_pass<C>()) {
-    constexpr int NB1 = C::N / C::rad[1];
-    static_assert(NB1 % R == 0 && ns_fwd<C>(1) == R, "split pass after the first pass");
-    const float4* tb = reinterpret_cast<const float4*>(lds + C::LDS + small_tw_offset<C>(1) + (t / (NB1 / R)) * R);
-    dft_pow2<R, INV>(a);
-    wb[0] = a[0];
+    const float4* tb = reinterpret_cast<const float4*>(lds + C::LDS + (t / R) * R);
     sfor<0, R / 2>([&](auto hv) {
       constexpr int h = decltype(hv)::value;
       const float4 q = tb[h];
-      if constexpr (h > 0) wb[2 * h] = twmul<INV>(a[2 * h], make_float2(q.x, q.y));
-      wb[2 * h + 1] = twmul<INV>(a[2 * h + 1], make_float2(q.z, q.w));
+      if constexpr (h > 0) a[2 * h] = twmul<INV>(a[2 * h], make_float2(q.x, q.y));
+      a[2 * h + 1] = twmul<INV>(a[2 * h + 1], make_float2(q.z, q.w));
     });
-  } else if constexpr (lane_perm<C>()) {
-    static_assert(C::PW % 2 == 0 && (C::PG / R) % 2 == 0, "16-byte aligned output pairs");
-    float2 o[R];
-    dft<R, INV>(a, [&](int q, float2 v) { o[q] = v; });
-    float4* w4 = reinterpret_cast<float4*>(wb);
-    sfor<0, R / 2>([&](auto hv) {
-      constexpr int h = decltype(hv)::value;
-      w4[h] = make_float4(o[2 * h].x, o[2 * h].y, o[2 * h + 1].x, o[2 * h + 1].y);
-    });
-  } else {
-    dft<R, INV>(a, [&](int q, float2 v) { wb[q] = v; });
   }
+  float2* wb = lds + t;
+  sfor<0, R>([&](auto qv) { wb[decltype(qv)::value * C::S1] = a[decltype(qv)::value]; });
 }
 
-// z <- P z on the resident path.  Threads past the last radix-R0 butterfly (T > N/R0, only
-// with a split pass) take part in the split pass and the barriers only.
+// z <- P z on the resident path.  Threads past the last outer butterfly (T > N/R0) take part in the
+// inner pass and the barriers only.
 template <class C, class RR>
 __device__ __forceinline__ void apply_P_res(float2 (&z)[C::E], float2* lds, RR& rr) {
-  constexpr int N = C::N;
   constexpr int R = C::R0;
-  constexpr int NB = N / R;
-  const int t = opaque(bfly<C>(threadIdx.x));
-  const bool act = (C::T == NB) || t < NB;
+  constexpr int NB = C::NB0;
+  constexpr int H = R / 2;
+  const bool act = (C::T == NB) || threadIdx.x < NB;
   // forward pass 0 (stride 1): registers -> LDS
   if (act) {
     float2 a[R];
     sfor<0, R>([&](auto rv) { a[decltype(rv)::value] = z[decltype(rv)::value]; });
-    res_first_pass<C, false>(a, lds, t);
+    res_first_pass<C, false>(a, lds, opaque(threadIdx.x));
   }
   __syncthreads();
-  res_inner_passes<C, 1, false>(lds, t);
+  res_inner<C, false>(lds);
   // forward last pass (stride N/R), fused with the eps step and the inverse first pass
   float2 y[R];
-  const float2* rb = lds + pad<C>(t);
-  // the last pass reads and writes the same elements t + q N/R, which no other thread touches:
-  // no barrier between its read and its write
-  if (act) sfor<0, R>([&](auto rv) { y[decltype(rv)::value] = rb[decltype(rv)::value * pad<C>(NB)]; });
+  const int t = opaque(threadIdx.x);
+  float4* rb = reinterpret_cast<float4*>(lds) + t;
+  // the last pass reads and writes column t, which no other thread touches: no barrier between its
+  // read and its write
+  if (act) {
+    sfor<0, H>([&](auto hv) {
+      constexpr int h = decltype(hv)::value;
+      const float4 q = rb[h * C::S2];
+      y[2 * h] = make_float2(q.x, q.y);
+      y[2 * h + 1] = make_float2(q.z, q.w);
+    });
+  }
   launder_powers<C>(rr);
   if (act) {
-    dft_pow2_tw<R, false>(y, [&](auto rv) { return last_tw<C, decltype(rv)::value>(rr); });  // y[q] = Y_{t + q NB}
-    float2* wb = lds + pad<C>(t);
-    sfor<0, R>([&](auto qv) { wb[decltype(qv)::value * pad<C>(NB)] = y[decltype(qv)::value]; });
+    dft_tw<R, false>(y, [&](auto rv) { return last_tw<C, decltype(rv)::value>(rr); });  // y[q] = Y_{t + q NB}
+    sfor<0, H>([&](auto hv) {
+      constexpr int h = decltype(hv)::value;
+      rb[h * C::S2] = make_float4(y[2 * h].x, y[2 * h].y, y[2 * h + 1].x, y[2 * h + 1].y);
+    });
   }
   __syncthreads();
   if (act) {
-    // partner values Y_{N - t - q NB} (slot pad<C>(N - t) - q pad<C>(NB); for t = 0, q = 0 the
-    // slot just past the buffer is read but never used: k = 0 pairs with itself)
-    const float2* pb = lds + pad<C>(N - t);
+    // partner values Y_{N - t - q NB}: row R - 1 - q, column NB - t (thread 0 pairs q with R - q: its bases are one row further, and q = 0 reads the slot past the
+    // last row, which is not used since k = 0 pairs with itself).  The reads are issued ahead and used
+    // unconditionally: for a select alone the compiler reads under a lane mask, element by element.
+    const float2* pe = lds + (t == 0 ? H * 2 * C::S2 : (H - 1) * 2 * C::S2 + 2 * (NB - t) + 1);
+    const float2* po = lds + (H - 1) * 2 * C::S2 + (t == 0 ? 1 : 2 * (NB - t));
+    constexpr int D = R < 16 ? R : (R == 16 && compact_eps<C>() ? 4 : 16);  // reads in flight (fewer under a tight budget)
+    float2 o[D];
+    sfor<0, D>([&](auto qv) {
+      constexpr int q = decltype(qv)::value;
+      o[q] = (q & 1 ? po : pe)[-(q / 2) * 2 * C::S2];
+    });
     sfor<0, R>([&](auto qv) {
       constexpr int q = decltype(qv)::value;
+      float2 oth = o[q % D];
+      launder(oth);
+      if constexpr (q + D < R) o[q % D] = ((q + D) & 1 ? po : pe)[-((q + D) / 2) * 2 * C::S2];
       bool partner;
       const float2 fq = eps_factor<C, q>(rr.eps, partner);
-      const float2 own = y[q];
-      const float2 oth = pb[-q * pad<C>(NB)];
-      const float2 v = partner ? oth : own;
+      const float2 v = partner ? oth : y[q];
       y[q] = make_float2(fq.x * v.x - fq.y * v.y, fq.x * v.y + fq.y * v.x);
-      if constexpr (q % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // bound partner values in flight
+      if constexpr (q & 1) __builtin_amdgcn_sched_barrier(0);  // bound the values in flight
     });
   }
   __syncthreads();
   // inverse pass 0 (stride 1)
-  if (act) res_first_pass<C, true>(y, lds, t);
+  if (act) res_first_pass<C, true>(y, lds, opaque(threadIdx.x));
   __syncthreads();
-  res_inner_passes<C, 1, true>(lds, t);
+  res_inner<C, true>(lds);
   // inverse last pass (stride N/R): LDS -> registers
   launder_powers<C>(rr);
   if (act) {
-    sfor<0, R>([&](auto rv) { z[decltype(rv)::value] = rb[decltype(rv)::value * pad<C>(NB)]; });
-    dft_pow2_tw<R, true>(z, [&](auto rv) { return last_tw<C, decltype(rv)::value>(rr); });
+    const float4* zb = reinterpret_cast<const float4*>(lds) + opaque(threadIdx.x);
+    sfor<0, H>([&](auto hv) {
+      constexpr int h = decltype(hv)::value;
+      const float4 q = zb[h * C::S2];
+      z[2 * h] = make_float2(q.x, q.y);
+      z[2 * h + 1] = make_float2(q.z, q.w);
+    });
+    dft_tw<R, true>(z, [&](auto rv) { return last_tw<C, decltype(rv)::value>(rr); });
+  } else {  // threads without elements hold zeros, set here so that z is not live across the transform
+    sfor<0, R>([&](auto rv) { z[decltype(rv)::value] = make_float2(0.f, 0.f); });
   }
 }
 
@@ -1199,7 +1136,7 @@ __device__ __forceinline__ float2 greedy_step(float2 (&z)[C::E], float2 (&acc)[C
   const float ca = div_n<C::N>(s[0]);
   const float cb = div_n<C::N>(s[1]);
   if (trace != nullptr) {
-    const int tid = opaque(bfly<C>(threadIdx.x));
+    const int tid = opaque(threadIdx.x);
 #pragma unroll
     for (int i = 0; i < C::B0; ++i) {
       const int j = tid + C::T * i;
@@ -1236,7 +1173,7 @@ __device__ __forceinline__ float to_f32(bf16_t v) { return bf16_to_f32(v); }
 // that the element offsets are recomputed rather than kept live across the loop).
 template <class C, class IT>
 __device__ __forceinline__ void load_pair_t(float2 (&z)[C::E], const IT* __restrict__ w, int64_t ldw, int64_t ra,
-                                            int64_t rb, int tid = bfly<C>(threadIdx.x)) {
+                                            int64_t rb, int tid = threadIdx.x) {
   const IT* __restrict__ pa = w + ra * ldw;
   const IT* __restrict__ pb = w + (rb >= 0 ? rb : ra) * ldw;
 #pragma unroll
@@ -1260,7 +1197,7 @@ __device__ __forceinline__ void load_pair_t(float2 (&z)[C::E], const IT* __restr
 }
 
 template <class C, class F>
-__device__ __forceinline__ void for_each_elem(F&& f, int tid = bfly<C>(threadIdx.x)) {
+__device__ __forceinline__ void for_each_elem(F&& f, int tid = threadIdx.x) {
 #pragma unroll
   for (int i = 0; i < C::B0; ++i) {
     const int j = tid + C::T * i;
@@ -1313,7 +1250,7 @@ __device__ __forceinline__ void stage_pair_t(float2* lds, const IT* __restrict__
 template <class C, bool ROT, class F>
 __device__ __forceinline__ void load_pair_staged(const void* w, int dtype, int64_t ldw, int64_t ra, int64_t rb,
                                                  uint64_t seed, float scale, float2* lds, F&& f) {
-  const int tid = bfly<C>(threadIdx.x);
+  const int tid = threadIdx.x;
   __syncthreads();
   if (dtype == KASHIN_F16) stage_pair_t<C, ROT>(lds, static_cast<const __half*>(w), ldw, ra, rb, seed, tid);
   else if (dtype == KASHIN_BF16) stage_pair_t<C, ROT>(lds, static_cast<const bf16_t*>(w), ldw, ra, rb, seed, tid);
@@ -1330,7 +1267,7 @@ __device__ __forceinline__ void load_pair_staged(const void* w, int dtype, int64
 
 template <class C>
 __device__ __forceinline__ void load_pair(float2 (&z)[C::E], const void* w, int dtype, int64_t ldw, int64_t ra,
-                                          int64_t rb, int tid = bfly<C>(threadIdx.x)) {
+                                          int64_t rb, int tid = threadIdx.x) {
   if (dtype == KASHIN_F16) load_pair_t<C>(z, static_cast<const __half*>(w), ldw, ra, rb, tid);
   else if (dtype == KASHIN_BF16) load_pair_t<C>(z, static_cast<const bf16_t*>(w), ldw, ra, rb, tid);
   else load_pair_t<C>(z, static_cast<const float*>(w), ldw, ra, rb, tid);
@@ -1563,27 +1500,6 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
   };
 
   float2 z[C::E], vh[C::E];
-  constexpr bool VHM = vh_in_memory<C>();
-  float4 vhm[VHM ? C::E / 2 : 1];  // vhat between steps (VHM); a run-time index keeps it in memory
-  auto vh_store = [&]() {
-    if constexpr (VHM) {
-      const int b = opaque(0);
-#pragma unroll
-      for (int h = 0; h < C::E / 2; ++h)
-        vhm[b + h] = make_float4(vh[2 * h].x, vh[2 * h].y, vh[2 * h + 1].x, vh[2 * h + 1].y);
-    }
-  };
-  auto vh_load = [&]() {
-    if constexpr (VHM) {
-      const int b = opaque(0);
-#pragma unroll
-      for (int h = 0; h < C::E / 2; ++h) {
-        const float4 q = vhm[b + h];
-        vh[2 * h] = make_float2(q.x, q.y);
-        vh[2 * h + 1] = make_float2(q.z, q.w);
-      }
-    }
-  };
   if constexpr (ROT) {
 #pragma unroll
     for (int e = 0; e < C::E; ++e) z[e] = make_float2(0.f, 0.f);
@@ -1597,7 +1513,6 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
   normalise_pair<C>(z, red, slot, scale, unscale, bad_a, bad_b);
 #pragma unroll
   for (int e = 0; e < C::E; ++e) vh[e] = make_float2(0.f, 0.f);
-  vh_store();
 
   const int steps = 4 * a.iters;
   int8_t* trace = nullptr;
@@ -1608,7 +1523,7 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
   }
   // block-0 step sizes (equal in every lane): on the shapes whose block loop sits at its register
   // limit they wait for the epilogue in LDS rather than in registers across the loop
-  constexpr bool CS_LDS = has_split_pass<C>() || is_small_inner_pass<C>(1) || vh_in_memory<C>();
+  constexpr bool CS_LDS = C::RES && (C::R0 > 16 || C::W >= 4 || (C::M & (C::M - 1)) != 0);
   __shared__ float2 cs_lds[4];
   float2 cs_reg[4];
   float2* cs = CS_LDS ? cs_lds : cs_reg;
@@ -1631,17 +1546,14 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
     csum_u = cadd(csum_u, c);
     // two steps on P Q_N, in the z = P rho domain, accumulating into vhat
     applyP(z);
-    vh_load();
     c = greedy_step<C, true>(z, vh, red, slot, tr ? tr + 2 * C::N : nullptr, side);
     step(t, 2, c);
     csum_v = cadd(csum_v, c);
     c = greedy_step<C, true>(z, vh, red, slot, tr ? tr + 3 * C::N : nullptr, side);
     step(t, 3, c);
     csum_v = cadd(csum_v, c);
-    vh_store();
   }
 
-  vh_load();
   if constexpr (CS_LDS) __syncthreads();  // cs (written by thread 0 in the first block) visible to all
   // Epilogue.  vhat is consumed first (written out, or clustered into codes) so that it is
   // not live while u = w - P(z + vhat) is formed: the register peak stays that of the loop.
@@ -1807,7 +1719,7 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
   for (int64_t it = first; it < nitems; it += stride) {
     const int64_t ra = 2 * (item0 + it);
     const int64_t rb = (ra + 1 < a.m) ? ra + 1 : -1;
-    const int tid = opaque(bfly<C>(threadIdx.x));
+    const int tid = opaque(threadIdx.x);
     float2 z[C::E];
 #pragma unroll
     for (int e = 0; e < C::E; ++e) z[e] = make_float2(0.f, 0.f);
@@ -2148,7 +2060,7 @@ pair_schedule_kernel(KArgs a, int64_t item0) {
     if constexpr (tracing) {
       const bool vs = side ? vb : va;
       const bool fs = side ? fb : fa;
-      const int tid = opaque(bfly<C>(threadIdx.x));
+      const int tid = opaque(threadIdx.x);
       int8_t* trs = a.tr_signs + (item * steps + st) * int64_t(C::N);
 #pragma unroll
       for (int i = 0; i < C::B0; ++i) {
