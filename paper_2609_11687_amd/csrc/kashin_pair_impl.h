@@ -882,9 +882,12 @@ __device__ __forceinline__ void res_inner_pass(float2* __restrict__ lds) {
 // Split inner pass: odd radix R = M, R0^2 butterflies, each shared by S = T / R0^2 threads
 // t = l + s R0^2 (s is uniform across a wave).  Every sub-group streams the R inputs of butterfly l
 // from LDS once, forming the pair sums and differences a_r +- a_{R-r}, and accumulates only its own
-// share of the (R-1)/2 output pairs (q, R-q); the twiddles were applied by the pass before.  All
-// sub-groups run one code path: their DFT constants come from a table in constant memory at a
-// wave-uniform address (scalar loads into SGPR operands of the FMAs).
+// share of the (R-1)/2 output pairs (q, R-q); the twiddles were applied by the pass before.  Each
+// sub-group has code of its own with the DFT constants as literals: an FMA with a literal issues
+// in two clocks, one with a scalar register (a shared code path with the constants in SGPRs) in
+// four, and the 588 FMAs a thread spends here were over half of the N = 11008 kernel's VALU time.
+// One copy of that code serves both directions (apply_P_split), so that the block loop stays in
+// the instruction cache.
 template <class C>
 struct SplitShape {
   static constexpr int R = C::M;
@@ -894,108 +897,74 @@ struct SplitShape {
   static constexpr int QP = (H + S - 1) / S;  // output pairs per sub-group
 };
 
-// {cos, sin}(2 pi r q / R) for sub-group s, input pair r = 1..H and output pair
-// q = s QP + 1 + i, at [((s H + r - 1) QP + i) 2] (zero past the last pair).
-template <int R, int S>
-struct SplitCoef {
-  static constexpr int H = (R - 1) / 2;
-  static constexpr int QP = (H + S - 1) / S;
-  float v[S * H * QP * 2];
-};
-template <int R, int S>
-constexpr SplitCoef<R, S> make_split_coef() {
-  SplitCoef<R, S> t{};
-  constexpr int H = SplitCoef<R, S>::H, QP = SplitCoef<R, S>::QP;
-  for (int s = 0; s < S; ++s)
-    for (int r = 1; r <= H; ++r)
-      for (int i = 0; i < QP; ++i) {
-        const int q = s * QP + 1 + i;
-        const int idx = ((s * H + r - 1) * QP + i) * 2;
-        if (q <= H) {
-          t.v[idx] = CisTab<R>::c[(r * q) % R];
-          t.v[idx + 1] = CisTab<R>::s[(r * q) % R];
-        }
-      }
-  return t;
-}
-template <int R, int S>
-__constant__ SplitCoef<R, S> split_coef = make_split_coef<R, S>();
-
-template <class C, bool INV>
-__device__ __forceinline__ void split_pass(float2* __restrict__ lds) {
-  const int t = opaque(threadIdx.x);
+// sub-group SG's outputs: re +- i im for its pairs (q, R - q), and the sum of all inputs
+template <class C, int SG>
+__device__ __forceinline__ void split_accumulate(const float2* __restrict__ rb, float2 (&re)[SplitShape<C>::QP],
+                                                 float2 (&im)[SplitShape<C>::QP], float2& sum) {
   using SS = SplitShape<C>;
-  constexpr int R = SS::R;
-  constexpr int NB = SS::NB;
-  constexpr int S = SS::S;
-  constexpr int QP = SS::QP;
-  constexpr int H = SS::H;
-  constexpr int R0 = C::R0;
-  static_assert(R % 2 == 1 && NB % 64 == 0 && C::T % NB == 0 && S <= H, "split pass shape");
-  const int s = __builtin_amdgcn_readfirstlane(t / NB);  // uniform across a wave
-  const InnerLane<C> il(t - s * NB);
-  const float* __restrict__ cf = split_coef<R, S>.v + s * (H * QP * 2);
-  const float2* rb = lds + il.rd;
+  constexpr int R = SS::R, H = SS::H, QP = SS::QP, R0 = C::R0;
+  constexpr int D = 3;  // input pairs in flight
   const float2 x0 = rb[0];
-  float2 re[QP], im[QP];
+  float2 p[D], m[D];
+  sfor<0, D>([&](auto cv) {
+    constexpr int c = decltype(cv)::value;
+    p[c] = rb[(c + 1) * R0];
+    m[c] = rb[(R - 1 - c) * R0];
+  });
   sfor<0, QP>([&](auto iv) {
     re[decltype(iv)::value] = x0;
     im[decltype(iv)::value] = make_float2(0.f, 0.f);
   });
-  float2 sum = x0;
-  // Input pairs, software-pipelined: the LDS reads and constant loads of pair r + 1 are issued after
-  // an explicit wait for those of pair r, so that the wait (LDS and scalar loads share one counter,
-  // and scalar loads return out of order) never covers loads that were just issued; pair r's FMAs
-  // then run while pair r + 1's loads are in flight.
-  float2 pin[2], mnn[2];
-  float cin[2][2 * QP];
-  auto fetch = [&](auto cv) {
-    constexpr int c = decltype(cv)::value;
-    constexpr int r = c + 1;
-    pin[c % 2] = rb[r * R0];
-    mnn[c % 2] = rb[(R - r) * R0];
-    sfor<0, 2 * QP>([&](auto ev) { cin[c % 2][decltype(ev)::value] = cf[c * QP * 2 + decltype(ev)::value]; });
-  };
-  fetch(std::integral_constant<int, 0>{});
+  sum = x0;
   sfor<0, H>([&](auto cv) {
     constexpr int c = decltype(cv)::value;
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): pair c's values are in registers
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (c + 1 < H) fetch(std::integral_constant<int, c + 1>{});
-    __builtin_amdgcn_sched_barrier(0);
-    const float2 p = pin[c % 2], m = mnn[c % 2];
-    const float2 sp = cadd(p, m), dm = csub(p, m);
-    sum = cadd(sum, sp);
+    constexpr int r = c + 1;
+    const float2 sp = cadd(p[c % D], m[c % D]), dm = csub(p[c % D], m[c % D]);
+    if constexpr (c + D < H) {
+      p[c % D] = rb[(r + D) * R0];
+      m[c % D] = rb[(R - r - D) * R0];
+    }
+    if constexpr (SG == 0) sum = cadd(sum, sp);
     sfor<0, QP>([&](auto iv) {
       constexpr int i = decltype(iv)::value;
-      const float cc = cin[c % 2][2 * i], sn = cin[c % 2][2 * i + 1];
-      re[i].x = fmaf(sp.x, cc, re[i].x);
-      re[i].y = fmaf(sp.y, cc, re[i].y);
-      im[i].x = fmaf(dm.x, sn, im[i].x);
-      im[i].y = fmaf(dm.y, sn, im[i].y);
+      constexpr int q = SG * QP + 1 + i;
+      if constexpr (q <= H) {
+        constexpr float cc = CisTab<R>::c[(r * q) % R], sn = CisTab<R>::s[(r * q) % R];
+        re[i].x = fmaf(sp.x, cc, re[i].x);
+        re[i].y = fmaf(sp.y, cc, re[i].y);
+        im[i].x = r == 1 ? dm.x * sn : fmaf(dm.x, sn, im[i].x);
+        im[i].y = r == 1 ? dm.y * sn : fmaf(dm.y, sn, im[i].y);
+      }
     });
+    __builtin_amdgcn_sched_barrier(0);  // bound the values in flight
   });
-  __syncthreads();
-  // forward: A_q = re - i im, A_{R-q} = re + i im; the inverse swaps them
-  const int q0 = s * QP + 1;
-  float2* wb = lds + il.wr;
-  sfor<0, QP>([&](auto iv) {
-    constexpr int i = decltype(iv)::value;
-    const float2 minus = make_float2(re[i].x + im[i].y, re[i].y - im[i].x);
-    const float2 plus = make_float2(re[i].x - im[i].y, re[i].y + im[i].x);
-    if (H % QP == 0 || q0 + i <= H) {
-      wb[(q0 + i) * 2 * R0] = INV ? plus : minus;
-      wb[(R - q0 - i) * 2 * R0] = INV ? minus : plus;
-    }
-  });
-  if (s == 0) wb[0] = sum;
-  __syncthreads();
 }
 
-template <class C, bool INV>
-__device__ __forceinline__ void res_inner(float2* lds) {
-  if constexpr (has_split_pass<C>()) split_pass<C, INV>(lds);
-  else res_inner_pass<C, INV>(lds);
+template <class C>
+__device__ __forceinline__ void split_pass(float2* __restrict__ lds, bool inv) {
+  using SS = SplitShape<C>;
+  constexpr int R = SS::R, NB = SS::NB, S = SS::S, QP = SS::QP, H = SS::H, R0 = C::R0;
+  static_assert(R % 2 == 1 && NB % 64 == 0 && C::T % NB == 0 && S == 3 && H % S == 0, "split pass shape");
+  const int t = opaque(threadIdx.x);
+  const int s = __builtin_amdgcn_readfirstlane(t / NB);  // uniform across a wave
+  const InnerLane<C> il(t - s * NB);
+  float2 re[QP], im[QP], sum;
+  if (s == 0) split_accumulate<C, 0>(lds + il.rd, re, im, sum);
+  else if (s == 1) split_accumulate<C, 1>(lds + il.rd, re, im, sum);
+  else split_accumulate<C, 2>(lds + il.rd, re, im, sum);
+  __syncthreads();
+  // forward: A_q = re - i im, A_{R-q} = re + i im; the inverse swaps them, by where they are written
+  const int q0 = s * QP + 1;
+  float2* wm = lds + il.wr + (inv ? R - q0 : q0) * 2 * R0;
+  float2* wp = lds + il.wr + (inv ? q0 : R - q0) * 2 * R0;
+  const int st = inv ? -2 * R0 : 2 * R0;
+  sfor<0, QP>([&](auto iv) {
+    constexpr int i = decltype(iv)::value;
+    wm[i * st] = make_float2(re[i].x + im[i].y, re[i].y - im[i].x);
+    wp[-i * st] = make_float2(re[i].x - im[i].y, re[i].y + im[i].x);
+  });
+  if (s == 0) lds[il.wr] = sum;
+  __syncthreads();
 }
 
 // First pass (stride 1) of either direction: a[] -> LDS.  When the inner pass is split its input
@@ -1018,39 +987,28 @@ __device__ __forceinline__ void res_first_pass(float2 (&a)[C::R0], float2* lds, 
   sfor<0, R>([&](auto qv) { wb[decltype(qv)::value * C::S1] = a[decltype(qv)::value]; });
 }
 
-// z <- P z on the resident path.  Threads past the last outer butterfly (T > N/R0) take part in the
-// inner pass and the barriers only.
+// Column t of the inner -> last layout: the inputs of the last pass's butterfly t.
+template <class C>
+__device__ __forceinline__ void res_read_column(float2 (&v)[C::R0], const float2* lds, int t) {
+  const float4* rb = reinterpret_cast<const float4*>(lds) + t;
+  sfor<0, C::R0 / 2>([&](auto hv) {
+    constexpr int h = decltype(hv)::value;
+    const float4 q = rb[h * C::S2];
+    v[2 * h] = make_float2(q.x, q.y);
+    v[2 * h + 1] = make_float2(q.z, q.w);
+  });
+}
+
+// The fused step between the transforms: y[q] = Y_{t + q NB} -> f_k Y_{s(k)}, the values of
+// thread N/R0 - t through LDS.  Column t is read and written by thread t alone before the barrier.
+// Called by every thread; those without elements (act false) take part in the barriers.
 template <class C, class RR>
-__device__ __forceinline__ void apply_P_res(float2 (&z)[C::E], float2* lds, RR& rr) {
+__device__ __forceinline__ void res_eps_step(float2 (&y)[C::R0], float2* lds, const RR& rr, int t, bool act) {
   constexpr int R = C::R0;
   constexpr int NB = C::NB0;
   constexpr int H = R / 2;
-  const bool act = (C::T == NB) || threadIdx.x < NB;
-  // forward pass 0 (stride 1): registers -> LDS
   if (act) {
-    float2 a[R];
-    sfor<0, R>([&](auto rv) { a[decltype(rv)::value] = z[decltype(rv)::value]; });
-    res_first_pass<C, false>(a, lds, opaque(threadIdx.x));
-  }
-  __syncthreads();
-  res_inner<C, false>(lds);
-  // forward last pass (stride N/R), fused with the eps step and the inverse first pass
-  float2 y[R];
-  const int t = opaque(threadIdx.x);
-  float4* rb = reinterpret_cast<float4*>(lds) + t;
-  // the last pass reads and writes column t, which no other thread touches: no barrier between its
-  // read and its write
-  if (act) {
-    sfor<0, H>([&](auto hv) {
-      constexpr int h = decltype(hv)::value;
-      const float4 q = rb[h * C::S2];
-      y[2 * h] = make_float2(q.x, q.y);
-      y[2 * h + 1] = make_float2(q.z, q.w);
-    });
-  }
-  launder_powers<C>(rr);
-  if (act) {
-    dft_tw<R, false>(y, [&](auto rv) { return last_tw<C, decltype(rv)::value>(rr); });  // y[q] = Y_{t + q NB}
+    float4* rb = reinterpret_cast<float4*>(lds) + t;
     sfor<0, H>([&](auto hv) {
       constexpr int h = decltype(hv)::value;
       rb[h * C::S2] = make_float4(y[2 * h].x, y[2 * h].y, y[2 * h + 1].x, y[2 * h + 1].y);
@@ -1058,12 +1016,14 @@ __device__ __forceinline__ void apply_P_res(float2 (&z)[C::E], float2* lds, RR& 
   }
   __syncthreads();
   if (act) {
-    // partner values Y_{N - t - q NB}: row R - 1 - q, column NB - t (thread 0 pairs q with R - q: its bases are one row further, and q = 0 reads the slot past the
-    // last row, which is not used since k = 0 pairs with itself).  The reads are issued ahead and used
-    // unconditionally: for a select alone the compiler reads under a lane mask, element by element.
+    // partner values Y_{N - t - q NB}: row R - 1 - q, column NB - t (thread 0 pairs q with R - q: its
+    // bases are one row further, and q = 0 reads the slot past the last row, which is not used
+    // since k = 0 pairs with itself).  The reads are issued ahead and used unconditionally: for a
+    // select alone the compiler reads under a lane mask, element by element.
     const float2* pe = lds + (t == 0 ? H * 2 * C::S2 : (H - 1) * 2 * C::S2 + 2 * (NB - t) + 1);
     const float2* po = lds + (H - 1) * 2 * C::S2 + (t == 0 ? 1 : 2 * (NB - t));
-    constexpr int D = R < 16 ? R : (R == 16 && compact_eps<C>() ? 4 : 16);  // reads in flight (fewer under a tight budget)
+    // reads in flight (fewer under a tight register budget)
+    constexpr int D = R < 16 ? R : (R == 16 && compact_eps<C>() ? 4 : (R > 16 ? 8 : 16));
     float2 o[D];
     sfor<0, D>([&](auto qv) {
       constexpr int q = decltype(qv)::value;
@@ -1082,20 +1042,67 @@ __device__ __forceinline__ void apply_P_res(float2 (&z)[C::E], float2* lds, RR& 
     });
   }
   __syncthreads();
-  // inverse pass 0 (stride 1)
+}
+
+// apply_P_res with a split inner pass: both transforms in one loop, so that the split pass's code
+// (16 KB for its three sub-groups) is there once.
+template <class C, class RR>
+__device__ __forceinline__ void apply_P_split(float2 (&z)[C::E], float2* lds, RR& rr) {
+  constexpr int R = C::R0;
+  const bool act = (C::T == C::NB0) || threadIdx.x < C::NB0;
+#pragma unroll 1
+  for (int dir = 0; dir < 2; ++dir) {
+    if (act) {
+      if (dir == 0) res_first_pass<C, false>(z, lds, opaque(threadIdx.x));
+      else res_first_pass<C, true>(z, lds, opaque(threadIdx.x));
+    }
+    __syncthreads();
+    split_pass<C>(lds, dir != 0);
+    const int t = opaque(threadIdx.x);
+    launder_powers<C>(rr);
+    if (act) {
+      res_read_column<C>(z, lds, t);
+      if (dir == 0) dft_tw<R, false>(z, [&](auto rv) { return last_tw<C, decltype(rv)::value>(rr); });
+      else dft_tw<R, true>(z, [&](auto rv) { return last_tw<C, decltype(rv)::value>(rr); });
+    } else {
+      sfor<0, R>([&](auto rv) { z[decltype(rv)::value] = make_float2(0.f, 0.f); });
+    }
+    if (dir == 0) res_eps_step<C>(z, lds, rr, t, act);
+  }
+}
+
+// z <- P z on the resident path.  Threads past the last outer butterfly (T > N/R0) take part in the
+// inner pass and the barriers only.
+template <class C, class RR>
+__device__ __forceinline__ void apply_P_res(float2 (&z)[C::E], float2* lds, RR& rr) {
+  constexpr int R = C::R0;
+  if constexpr (has_split_pass<C>()) {
+    apply_P_split<C>(z, lds, rr);
+    return;
+  }
+  const bool act = (C::T == C::NB0) || threadIdx.x < C::NB0;
+  // forward first pass (stride 1): registers -> LDS
+  if (act) {
+    float2 a[R];
+    sfor<0, R>([&](auto rv) { a[decltype(rv)::value] = z[decltype(rv)::value]; });
+    res_first_pass<C, false>(a, lds, opaque(threadIdx.x));
+  }
+  __syncthreads();
+  res_inner_pass<C, false>(lds);
+  // forward last pass (stride N/R0), fused with the eps step and the inverse first pass
+  float2 y[R];
+  const int t = opaque(threadIdx.x);
+  if (act) res_read_column<C>(y, lds, t);
+  launder_powers<C>(rr);
+  if (act) dft_tw<R, false>(y, [&](auto rv) { return last_tw<C, decltype(rv)::value>(rr); });
+  res_eps_step<C>(y, lds, rr, t, act);
   if (act) res_first_pass<C, true>(y, lds, opaque(threadIdx.x));
   __syncthreads();
-  res_inner<C, true>(lds);
-  // inverse last pass (stride N/R): LDS -> registers
+  res_inner_pass<C, true>(lds);
+  // inverse last pass: LDS -> registers
   launder_powers<C>(rr);
   if (act) {
-    const float4* zb = reinterpret_cast<const float4*>(lds) + opaque(threadIdx.x);
-    sfor<0, H>([&](auto hv) {
-      constexpr int h = decltype(hv)::value;
-      const float4 q = zb[h * C::S2];
-      z[2 * h] = make_float2(q.x, q.y);
-      z[2 * h + 1] = make_float2(q.z, q.w);
-    });
+    res_read_column<C>(z, lds, opaque(threadIdx.x));
     dft_tw<R, true>(z, [&](auto rv) { return last_tw<C, decltype(rv)::value>(rr); });
   } else {  // threads without elements hold zeros, set here so that z is not live across the transform
     sfor<0, R>([&](auto rv) { z[decltype(rv)::value] = make_float2(0.f, 0.f); });
@@ -1534,24 +1541,42 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
       if (trc != nullptr && threadIdx.x == 0) trc[4 * t + st] = (side ? c.y : c.x) * (side ? unscale.y : unscale.x);
     }
   };
-  for (int t = 0; t < a.iters; ++t) {
-    if (t > 0) applyP(z);  // back to the residual rho
+  // half-block h = 2t: two steps on the cube Q_N, accumulating into u (u itself is recovered at the
+  // end); h = 2t + 1: two steps on P Q_N, in the z = P rho domain, accumulating into vhat.  P between
+  // any two half-blocks (P^2 = I)
+  auto half_u = [&](int t) {
     int8_t* tr = trace ? trace + int64_t(4 * t) * C::N : nullptr;
-    // two steps on the cube Q_N, accumulating into u (u itself is recovered at the end)
     float2 c = greedy_step<C, false>(z, vh, red, slot, tr, side);
     step(t, 0, c);
     csum_u = cadd(csum_u, c);
     c = greedy_step<C, false>(z, vh, red, slot, tr ? tr + C::N : nullptr, side);
     step(t, 1, c);
     csum_u = cadd(csum_u, c);
-    // two steps on P Q_N, in the z = P rho domain, accumulating into vhat
-    applyP(z);
-    c = greedy_step<C, true>(z, vh, red, slot, tr ? tr + 2 * C::N : nullptr, side);
+  };
+  auto half_v = [&](int t) {
+    int8_t* tr = trace ? trace + int64_t(4 * t + 2) * C::N : nullptr;
+    float2 c = greedy_step<C, true>(z, vh, red, slot, tr, side);
     step(t, 2, c);
     csum_v = cadd(csum_v, c);
-    c = greedy_step<C, true>(z, vh, red, slot, tr ? tr + 3 * C::N : nullptr, side);
+    c = greedy_step<C, true>(z, vh, red, slot, tr ? tr + C::N : nullptr, side);
     step(t, 3, c);
     csum_v = cadd(csum_v, c);
+  };
+  if constexpr (has_split_pass<C>()) {
+    // one copy of P's code (see split_pass)
+#pragma unroll 1
+    for (int h = 0; h < 2 * a.iters; ++h) {
+      if (h > 0) applyP(z);
+      if (h & 1) half_v(h >> 1);
+      else half_u(h >> 1);
+    }
+  } else {
+    for (int t = 0; t < a.iters; ++t) {
+      if (t > 0) applyP(z);
+      half_u(t);
+      applyP(z);
+      half_v(t);
+    }
   }
 
   if constexpr (CS_LDS) __syncthreads();  // cs (written by thread 0 in the first block) visible to all
