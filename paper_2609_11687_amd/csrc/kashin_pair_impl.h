@@ -430,7 +430,7 @@ __device__ __forceinline__ void block_sum(float (&v)[K], float* red, int& slot) 
 #pragma unroll
       for (int k = 0; k < K; ++k) r[(threadIdx.x >> 6) * K + k] = v[k];
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       float s = r[k];
@@ -459,7 +459,7 @@ __device__ __forceinline__ void block_sum_lanes(float (&v)[K], float* red, int& 
 #pragma unroll
       for (int k = 0; k < K; ++k) r[(threadIdx.x >> 6) * K + k] = v[k];
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       float t = lane < NW ? r[lane * K + k] : 0.f;
@@ -484,7 +484,7 @@ __device__ __forceinline__ void block_max(float (&v)[K], float* red, int& slot) 
 #pragma unroll
       for (int k = 0; k < K; ++k) r[(threadIdx.x >> 6) * K + k] = v[k];
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       float s = r[k];
@@ -570,7 +570,7 @@ __device__ __forceinline__ void fft_pass(float2 (&z)[C::E], float2* __restrict__
       }
     }
   });
-  if constexpr (SRC != SRC_REGS) __syncthreads();
+  if constexpr (SRC != SRC_REGS) lds_barrier();
   sfor<0, BP>([&](auto iv) {
     constexpr int i = decltype(iv)::value;
     const int j = tid + T * i;
@@ -622,7 +622,7 @@ __device__ __forceinline__ void fft_pass(float2 (&z)[C::E], float2* __restrict__
       }
     }
   });
-  if constexpr (DST == DST_LDS) __syncthreads();
+  if constexpr (DST == DST_LDS) lds_barrier();
 }
 
 template <class C, int P>
@@ -814,7 +814,7 @@ __device__ __forceinline__ void resident_load(RR& rr, float2* lds, const float2*
     const int at = has_split_pass<C>() ? r * R + jm : 2 * ((r / 2) * R + jm) + (r & 1);
     small[at] = tw[tw_offset<C, false>(1) + i];
   }
-  __syncthreads();
+  lds_barrier();
 }
 
 // Butterfly (jh, jm) = jh R0 + jm of the inner pass that lane l takes: lanes run over the low bit of
@@ -858,7 +858,7 @@ __device__ __forceinline__ void res_inner_pass(float2* __restrict__ lds) {
       }
     }
   });
-  __syncthreads();
+  lds_barrier();
   sfor<0, BPT>([&](auto iv) {
     constexpr int i = decltype(iv)::value;
     const int l = t + C::T * i;
@@ -876,7 +876,7 @@ __device__ __forceinline__ void res_inner_pass(float2* __restrict__ lds) {
       sfor<0, M>([&](auto qv) { wb[decltype(qv)::value * 2 * R0] = a[i][decltype(qv)::value]; });
     }
   });
-  __syncthreads();
+  lds_barrier();
 }
 
 // Split inner pass: odd radix R = M, R0^2 butterflies, each shared by S = T / R0^2 threads
@@ -952,7 +952,7 @@ __device__ __forceinline__ void split_pass(float2* __restrict__ lds, bool inv) {
   if (s == 0) split_accumulate<C, 0>(lds + il.rd, re, im, sum);
   else if (s == 1) split_accumulate<C, 1>(lds + il.rd, re, im, sum);
   else split_accumulate<C, 2>(lds + il.rd, re, im, sum);
-  __syncthreads();
+  lds_barrier();
   // forward: A_q = re - i im, A_{R-q} = re + i im; the inverse swaps them, by where they are written
   const int q0 = s * QP + 1;
   float2* wm = lds + il.wr + (inv ? R - q0 : q0) * 2 * R0;
@@ -964,7 +964,7 @@ __device__ __forceinline__ void split_pass(float2* __restrict__ lds, bool inv) {
     wp[-i * st] = make_float2(re[i].x - im[i].y, re[i].y + im[i].x);
   });
   if (s == 0) lds[il.wr] = sum;
-  __syncthreads();
+  lds_barrier();
 }
 
 // First pass (stride 1) of either direction: a[] -> LDS.  When the inner pass is split its input
@@ -1014,7 +1014,7 @@ __device__ __forceinline__ void res_eps_step(float2 (&y)[C::R0], float2* lds, co
       rb[h * C::S2] = make_float4(y[2 * h].x, y[2 * h].y, y[2 * h + 1].x, y[2 * h + 1].y);
     });
   }
-  __syncthreads();
+  lds_barrier();
   if (act) {
     // partner values Y_{N - t - q NB}: row R - 1 - q, column NB - t (thread 0 pairs q with R - q: its
     // bases are one row further, and q = 0 reads the slot past the last row, which is not used
@@ -1041,7 +1041,7 @@ __device__ __forceinline__ void res_eps_step(float2 (&y)[C::R0], float2* lds, co
       if constexpr (q & 1) __builtin_amdgcn_sched_barrier(0);  // bound the values in flight
     });
   }
-  __syncthreads();
+  lds_barrier();
 }
 
 // apply_P_res with a split inner pass: both transforms in one loop, so that the split pass's code
@@ -1056,7 +1056,7 @@ __device__ __forceinline__ void apply_P_split(float2 (&z)[C::E], float2* lds, RR
       if (dir == 0) res_first_pass<C, false>(z, lds, opaque(threadIdx.x));
       else res_first_pass<C, true>(z, lds, opaque(threadIdx.x));
     }
-    __syncthreads();
+    lds_barrier();
     split_pass<C>(lds, dir != 0);
     const int t = opaque(threadIdx.x);
     launder_powers<C>(rr);
@@ -1087,7 +1087,7 @@ __device__ __forceinline__ void apply_P_res(float2 (&z)[C::E], float2* lds, RR& 
     sfor<0, R>([&](auto rv) { a[decltype(rv)::value] = z[decltype(rv)::value]; });
     res_first_pass<C, false>(a, lds, opaque(threadIdx.x));
   }
-  __syncthreads();
+  lds_barrier();
   res_inner_pass<C, false>(lds);
   // forward last pass (stride N/R0), fused with the eps step and the inverse first pass
   float2 y[R];
@@ -1097,7 +1097,7 @@ __device__ __forceinline__ void apply_P_res(float2 (&z)[C::E], float2* lds, RR& 
   if (act) dft_tw<R, false>(y, [&](auto rv) { return last_tw<C, decltype(rv)::value>(rr); });
   res_eps_step<C>(y, lds, rr, t, act);
   if (act) res_first_pass<C, true>(y, lds, opaque(threadIdx.x));
-  __syncthreads();
+  lds_barrier();
   res_inner_pass<C, true>(lds);
   // inverse last pass: LDS -> registers
   launder_powers<C>(rr);
@@ -1258,18 +1258,18 @@ template <class C, bool ROT, class F>
 __device__ __forceinline__ void load_pair_staged(const void* w, int dtype, int64_t ldw, int64_t ra, int64_t rb,
                                                  uint64_t seed, float scale, float2* lds, F&& f) {
   const int tid = threadIdx.x;
-  __syncthreads();
+  lds_barrier();
   if (dtype == KASHIN_F16) stage_pair_t<C, ROT>(lds, static_cast<const __half*>(w), ldw, ra, rb, seed, tid);
   else if (dtype == KASHIN_BF16) stage_pair_t<C, ROT>(lds, static_cast<const bf16_t*>(w), ldw, ra, rb, seed, tid);
   else stage_pair_t<C, ROT>(lds, static_cast<const float*>(w), ldw, ra, rb, seed, tid);
-  __syncthreads();
+  lds_barrier();
   if constexpr (ROT) {
     constexpr int B = rot_odd_part(C::N);
     rot_odd_factor_fixed<B, false, C::T, C::N>(lds, tid);
     rot_hadamard<B, C::T>(lds, C::N, tid);
   }
   for_each_elem<C>([&](int e, int i) { f(e, ROT ? rv_scale(lds[i], scale) : lds[i]); }, tid);
-  __syncthreads();
+  lds_barrier();
 }
 
 template <class C>
@@ -1417,12 +1417,12 @@ __device__ __forceinline__ void write_codes(const float2 (&x)[C::E], const float
   midpoints(q[0], mids[0]);
   midpoints(q[1], mids[1]);
   uint8_t* cb = reinterpret_cast<uint8_t*>(lds);
-  __syncthreads();  // the last FFT pass read this buffer without a closing barrier
+  lds_barrier();  // the last FFT pass read this buffer without a closing barrier
   for_each_elem<C>([&](int e, int i) {
     cb[i] = static_cast<uint8_t>(code_of(x[e].x, mids[0]));
     cb[C::N + i] = static_cast<uint8_t>(code_of(x[e].y, mids[1]));
   });
-  __syncthreads();
+  lds_barrier();
   constexpr int NBY = (C::N + 3) / 4;
   for (int b = threadIdx.x; b < NBY; b += C::T) {
 #pragma unroll
@@ -1438,7 +1438,7 @@ __device__ __forceinline__ void write_codes(const float2 (&x)[C::E], const float
       dst[row * NBY + b] = (sd ? bad_b : bad_a) ? 0 : static_cast<uint8_t>(byte);
     }
   }
-  __syncthreads();
+  lds_barrier();
 }
 
 __device__ __forceinline__ void store_centers(float* centers, int f, const float (&q)[2][4], int64_t ra, int64_t rb,
@@ -1579,7 +1579,7 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
     }
   }
 
-  if constexpr (CS_LDS) __syncthreads();  // cs (written by thread 0 in the first block) visible to all
+  if constexpr (CS_LDS) lds_barrier();  // cs (written by thread 0 in the first block) visible to all
   // Epilogue.  vhat is consumed first (written out, or clustered into codes) so that it is
   // not live while u = w - P(z + vhat) is formed: the register peak stays that of the loop.
   const float qnan = __int_as_float(0x7fc00000);
@@ -1684,7 +1684,7 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
   }
   if (want_r) {
     // r = P z_final (the residual of Alg. 2), from the z saved above
-    __syncthreads();  // the saved z is read back by other threads of the workgroup
+    __syncthreads();  // the saved z (in global memory) is read back by other threads of the workgroup
     load_pair_t<C>(z, a.r, C::N, ra, rb);
     applyP(z);
     for_each_elem<C>([&](int e, int i) {
@@ -1775,9 +1775,9 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
       }
     }
     if (recon) {
-      __syncthreads();
+      lds_barrier();
       for_each_elem<C>([&](int e, int i) { z[e] = make_float2(lf[i], lf[N + i]); }, tid);
-      __syncthreads();  // the staged v_q rows are read before the first pass overwrites the buffer
+      lds_barrier();  // the staged v_q rows are read before the first pass overwrites the buffer
     }
     float2 scale, unscale;
     bool bad_a, bad_b;
@@ -1789,18 +1789,18 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
         a.y[ra * a.ldy + i] = bad_a ? qnan : z[e].x * unscale.x;
         if (rb >= 0) a.y[rb * a.ldy + i] = bad_b ? qnan : z[e].y * unscale.y;
       }, tid);
-      __syncthreads();  // the last pass read the buffer the next item's first pass writes
+      lds_barrier();  // the last pass read the buffer the next item's first pass writes
       continue;
     }
     if constexpr (ROT) {
       // w_hat = R^T (P v_q + u_q): both rows in row order as float2, u_q added, then the
       // Hadamard factor, C_b^T, the scale and the signs, as the standalone inverse rotation
       constexpr int B = rot_odd_part(N);
-      __syncthreads();  // the last pass read the buffer
+      lds_barrier();  // the last pass read the buffer
       for_each_elem<C>([&](int e, int i) {
         lds[i] = make_float2(bad_a ? qnan : z[e].x * unscale.x, bad_b ? qnan : z[e].y * unscale.y);
       }, tid);
-      __syncthreads();
+      lds_barrier();
       const uint8_t* cua = static_cast<const uint8_t*>(a.w) + ra * NBY;
       const uint8_t* cub = static_cast<const uint8_t*>(a.w) + (rb >= 0 ? rb : ra) * NBY;
       const float* cea = a.in_centers + ra * 8;
@@ -1817,7 +1817,7 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
           lds[4 * q + k] = v;
         }
       }
-      __syncthreads();
+      lds_barrier();
       rot_hadamard<B, C::T>(lds, N, tid);
       rot_odd_factor_fixed<B, true, C::T, N>(lds, tid);
       float* ya = a.y + ra * a.ldy;
@@ -1828,15 +1828,15 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
         ya[i] = v.x * a.rot_scale * s;
         if (rb >= 0) yb[i] = v.y * a.rot_scale * s;
       }
-      __syncthreads();  // read before the next item's first pass writes the buffer
+      lds_barrier();  // read before the next item's first pass writes the buffer
       continue;
     }
-    __syncthreads();  // the last pass read the buffer the outputs are staged in
+    lds_barrier();  // the last pass read the buffer the outputs are staged in
     for_each_elem<C>([&](int e, int i) {
       lf[i] = bad_a ? qnan : z[e].x * unscale.x;
       lf[N + i] = bad_b ? qnan : z[e].y * unscale.y;
     }, tid);
-    __syncthreads();
+    lds_barrier();
     // 2. reconstruction: w_hat = P v_q + u_q in row order, 16-byte stores
     const uint8_t* cua = static_cast<const uint8_t*>(a.w) + ra * NBY;
     const uint8_t* cub = static_cast<const uint8_t*>(a.w) + (rb >= 0 ? rb : ra) * NBY;
@@ -1873,7 +1873,7 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
         }
       }
     }
-    __syncthreads();  // staged outputs read before the next item stages its inputs
+    lds_barrier();  // staged outputs read before the next item stages its inputs
   }
 }
 
@@ -1887,13 +1887,13 @@ __device__ __forceinline__ void store_pair_staged(float2* lds, float* out_a, flo
   static_assert(C::N % 4 == 0, "rows staged as float4");
   float* lf = reinterpret_cast<float*>(lds);
   const float4* lf4 = reinterpret_cast<const float4*>(lds);
-  __syncthreads();  // earlier readers of the buffer are done
+  lds_barrier();  // earlier readers of the buffer are done
   for_each_elem<C>([&](int e, int i) {
     const float2 v = f(e);
     lf[i] = v.x;
     lf[C::N + i] = v.y;
   });
-  __syncthreads();
+  lds_barrier();
   const bool vec_a = (reinterpret_cast<uintptr_t>(out_a) & 15) == 0;
   const bool vec_b = (reinterpret_cast<uintptr_t>(out_b) & 15) == 0;
   for (int q = threadIdx.x; q < C::N / 4; q += C::T) {
@@ -1920,7 +1920,7 @@ __device__ __forceinline__ void store_pair_staged(float2* lds, float* out_a, flo
       }
     }
   }
-  __syncthreads();  // the staged rows are read before the buffer's next writer
+  lds_barrier();  // the staged rows are read before the buffer's next writer
 }
 
 // ------------------------------------------------------------------ schedule variants

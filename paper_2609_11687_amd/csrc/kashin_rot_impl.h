@@ -12,6 +12,15 @@
 
 namespace kashin {
 
+// Barrier that orders the workgroup's LDS accesses and nothing else.  __syncthreads also waits for
+// every global access of the wave, so in a kernel that walks rows it holds each row back until the
+// stores of the row before have reached memory.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // s_i: -1 when the top bit of the i-th splitmix64 output of `seed` is set
 __device__ __forceinline__ float rot_sign(uint64_t seed, int i) {
   uint64_t z = seed + static_cast<uint64_t>(i + 1) * 0x9E3779B97F4A7C15ull;
@@ -34,18 +43,50 @@ __device__ __forceinline__ float2 rv_sub(float2 a, float2 b) { return make_float
 __device__ __forceinline__ float rv_scale(float a, float s) { return a * s; }
 __device__ __forceinline__ float2 rv_scale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
 
+// The odd factor C_B by its symmetry m[k][B-1-j] = (-1)^k m[k][j]: with s_j = x_j + x_{B-1-j} and
+// d_j = x_j - x_{B-1-j} (j < H = (B-1)/2), output k of C_B x is sum_j m[k][j] s_j + m[k][H] x_H for even
+// k and sum_j m[k][j] d_j for odd k; outputs j and B-1-j of C_B^T x are E_j +- O_j, the sums over even
+// and odd k.  Half the products of the plain matrix (925 FMAs for B = 43 against 1849).  Every sum
+// runs in ascending order from zero, in the whole-segment and the chunked form alike, so the fused
+// and the standalone rotation agree bit for bit.
+
 // one segment of length B: v <- C_B v (or C_B^T v), in place, constants compile-time
 template <int B, bool TRANS, class V>
 __device__ __forceinline__ void rot_odd_segment(V* seg) {
+  constexpr int H = (B - 1) / 2;
   V in[B];
 #pragma unroll
   for (int j = 0; j < B; ++j) in[j] = seg[j];
+  if constexpr (!TRANS) {
 #pragma unroll
-  for (int k = 0; k < B; ++k) {
-    V acc = rv_zero(in[0]);
+    for (int j = 0; j < H; ++j) {
+      const V u = in[j], v = in[B - 1 - j];
+      in[j] = rv_add(u, v);
+      in[B - 1 - j] = rv_sub(u, v);
+    }
 #pragma unroll
-    for (int j = 0; j < B; ++j) acc = rv_fma(TRANS ? DctTab<B>::m[j * B + k] : DctTab<B>::m[k * B + j], in[j], acc);
-    seg[k] = acc;
+    for (int k = 0; k < B; ++k) {
+      V acc = rv_zero(in[0]);
+#pragma unroll
+      for (int j = 0; j < H; ++j) acc = rv_fma(DctTab<B>::m[k * B + j], k % 2 ? in[B - 1 - j] : in[j], acc);
+      if (k % 2 == 0) acc = rv_fma(DctTab<B>::m[k * B + H], in[H], acc);
+      seg[k] = acc;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j <= H; ++j) {
+      V e = rv_zero(in[0]), o = rv_zero(in[0]);
+#pragma unroll
+      for (int k = 0; k < B; k += 2) e = rv_fma(DctTab<B>::m[k * B + j], in[k], e);
+      if (j < H) {
+#pragma unroll
+        for (int k = 1; k < B; k += 2) o = rv_fma(DctTab<B>::m[k * B + j], in[k], o);
+        seg[B - 1 - j] = rv_sub(e, o);
+        seg[j] = rv_add(e, o);
+      } else {
+        seg[j] = e;
+      }
+    }
   }
 }
 
@@ -54,57 +95,93 @@ template <int B, bool TRANS, int T, class V>
 __device__ __forceinline__ void rot_odd_factor(V* buf, int n, int tid) {
   if constexpr (B > 1) {
     for (int i = tid; i < n / B; i += T) rot_odd_segment<B, TRANS>(buf + i * B);
-    __syncthreads();
+    lds_barrier();
   }
 }
 
-// outputs K0 .. K0 + KC - 1 (those below B) of C_B seg (or C_B^T seg), each accumulated over the
-// inputs in ascending order from zero, as rot_odd_segment does
-template <int B, bool TRANS, int K0, int KC, class V>
+// chunk c of C_B seg (or C_B^T seg) in acc: outputs c KC .. of C_B; of C_B^T the pairs (j, B-1-j),
+// j = c KC / 2 .., as E_j + O_j in acc[0 .. KC/2) and E_j - O_j in acc[KC/2 .. KC), the middle output
+// (j = H) being the last chunk's last pair
+template <int B, bool TRANS, int CH, int KC, class V>
 __device__ __forceinline__ void rot_odd_chunk(const V* seg, V (&acc)[KC]) {
+  constexpr int H = (B - 1) / 2;
 #pragma unroll
   for (int kk = 0; kk < KC; ++kk) acc[kk] = rv_zero(acc[0]);
+  if constexpr (!TRANS) {
 #pragma unroll
-  for (int j = 0; j < B; ++j) {
-    const V x = seg[j];
+    for (int j = 0; j <= H; ++j) {
+      const V u = seg[j], v = j < H ? seg[B - 1 - j] : u;
+      const V sm = j < H ? rv_add(u, v) : u, df = rv_sub(u, v);
 #pragma unroll
-    for (int kk = 0; kk < KC; ++kk) {
-      if (K0 + kk < B)
-        acc[kk] = rv_fma(TRANS ? DctTab<B>::m[j * B + K0 + kk] : DctTab<B>::m[(K0 + kk) * B + j], x, acc[kk]);
+      for (int kk = 0; kk < KC; ++kk) {
+        const int k = CH * KC + kk;
+        if (k < B && (j < H || k % 2 == 0)) acc[kk] = rv_fma(DctTab<B>::m[k * B + j], k % 2 ? df : sm, acc[kk]);
+      }
+    }
+  } else {
+    constexpr int JC = KC / 2;
+#pragma unroll
+    for (int k = 0; k < B; ++k) {
+      const V x = seg[k];
+#pragma unroll
+      for (int jj = 0; jj < JC; ++jj) {
+        const int j = CH * JC + jj;  // even k into acc[jj] (E_j), odd k into acc[JC + jj] (O_j)
+        if (j <= H && !(j == H && k % 2)) acc[(k % 2) * JC + jj] = rv_fma(DctTab<B>::m[k * B + j], x, acc[(k % 2) * JC + jj]);
+      }
+    }
+#pragma unroll
+    for (int jj = 0; jj < JC; ++jj) {
+      const V e = acc[jj], o = acc[JC + jj];
+      if (CH * JC + jj < H) {
+        acc[jj] = rv_add(e, o);
+        acc[JC + jj] = rv_sub(e, o);
+      }
     }
   }
 }
 
-// The odd factor for a length N known at compile time.  When the workgroup has at least twice
-// as many threads as segments and B is large, each segment's outputs are split into NC chunks
+// The odd factor for a length N known at compile time.  When the workgroup has at least three
+// times as many threads as segments and B is large, each segment's outputs are split into NC chunks
 // computed by NC threads (all inputs read before the barrier, outputs written after it), so that
 // more waves share the work and each holds fewer values; otherwise one thread per segment.
 template <int B, bool TRANS, int T, int N, class V>
 __device__ __forceinline__ void rot_odd_factor_fixed(V* buf, int tid) {
   constexpr int NSEG = N / B;
-  constexpr int NC = (B >= 16 && T >= 2 * NSEG) ? (T / NSEG < 3 ? T / NSEG : 3) : 1;
+  constexpr int NC = (B >= 16 && T >= 3 * NSEG) ? 3 : 1;
   if constexpr (NC == 1) {
     rot_odd_factor<B, TRANS, T>(buf, N, tid);
   } else {
-    constexpr int KC = (B + NC - 1) / NC;
+    constexpr int H = (B - 1) / 2;
+    constexpr int JC = (H + 1 + NC - 1) / NC;              // output pairs per chunk (TRANS)
+    constexpr int KC = TRANS ? 2 * JC : (B + NC - 1) / NC;  // values per chunk
     V acc[KC];
     const int c = tid / NSEG, sg = tid - c * NSEG;  // chunk and segment of this thread
     const V* seg = buf + sg * B;
     if (c == 0) {
       rot_odd_chunk<B, TRANS, 0, KC>(seg, acc);
     } else if (c == 1) {
-      rot_odd_chunk<B, TRANS, KC, KC>(seg, acc);
-    } else if (NC == 3 && c == 2) {
-      rot_odd_chunk<B, TRANS, 2 * KC, KC>(seg, acc);
+      rot_odd_chunk<B, TRANS, 1, KC>(seg, acc);
+    } else if (c == 2) {
+      rot_odd_chunk<B, TRANS, 2, KC>(seg, acc);
     }
-    __syncthreads();  // every input read before any output is written
+    lds_barrier();  // every input read before any output is written
     if (c < NC) {
-      V* out = buf + sg * B + c * KC;
+      if constexpr (TRANS) {
+        V* out = buf + sg * B + c * JC;
+        V* mir = buf + sg * B + B - 1 - c * JC;
 #pragma unroll
-      for (int kk = 0; kk < KC; ++kk)
-        if (c * KC + kk < B) out[kk] = acc[kk];
+        for (int jj = 0; jj < JC; ++jj) {
+          if (c * JC + jj <= H) out[jj] = acc[jj];
+          if (c * JC + jj < H) mir[-jj] = acc[JC + jj];
+        }
+      } else {
+        V* out = buf + sg * B + c * KC;
+#pragma unroll
+        for (int kk = 0; kk < KC; ++kk)
+          if (c * KC + kk < B) out[kk] = acc[kk];
+      }
     }
-    __syncthreads();
+    lds_barrier();
   }
 }
 
@@ -147,7 +224,7 @@ __device__ __forceinline__ void rot_hadamard_pass(V* buf, int n, int lh, int tid
 #pragma unroll
     for (int m = 0; m < R; ++m) p[m * st] = x[m];
   }
-  __syncthreads();
+  lds_barrier();
 }
 
 // unnormalised Walsh-Hadamard transform over the 2^a segments (stride B), in place: passes of
