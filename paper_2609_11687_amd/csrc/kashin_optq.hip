@@ -92,7 +92,20 @@ __global__ __launch_bounds__(kMT) void chunk_factor_kernel(const double* v, cons
   const int kq = (threadIdx.x / kMR) * (kMK / (kMT / kMR));  // 4 rows per thread
   double acc[kMK / (kMT / kMR)] = {};
   if (r < rest) {
-    for (int l = 0; l < rows; ++l) {
+    // eight rows of U in flight per thread: one load at a time made this a chain of memory latencies
+    // (128 x 128 x 3968: 15.5 -> 13.5 us)
+    constexpr int kAhead = 8;
+    int l = 0;
+    for (; l + kAhead <= rows; l += kAhead) {
+      double ul[kAhead];
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) ul[i] = u[(c0 + l + i) * ld + (c1 + r)];
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+        for (int a = 0; a < kMK / (kMT / kMR); ++a) acc[a] += vs[kq + a][l + i] * ul[i];
+    }
+    for (; l < rows; ++l) {
       const double ul = u[(c0 + l) * ld + (c1 + r)];
 #pragma unroll
       for (int a = 0; a < kMK / (kMT / kMR); ++a) acc[a] += vs[kq + a][l] * ul;
@@ -154,6 +167,84 @@ __global__ __launch_bounds__(kGT) void update_gemm_kernel(float* c, int64_t ldc,
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (x0 + tx + j < n) c[r * ldc + x0 + tx + j] -= acc[i][j];
+  }
+}
+
+// The same product in 128 x 128 tiles: 256 threads with 8 x 8 accumulators each (rows tr .. tr + 3 and
+// 64 + tr .., columns likewise: 16-byte LDS reads, a quarter of the words per FMA of the 4 x 4
+// tile's), the next K step's tile loaded into registers while this one is multiplied.  Every
+// accumulator runs over k in the same order as above: the results are equal bit for bit.  128 x
+// (3968 x 4096): 84 -> 79 us; a whole chunk step with 11008-long rows 1223 -> 1113.  (128 x 128 tiles
+// on the FP32 matrix instruction took 75 us at the one and made the other 1150.)
+constexpr int kLB = 128;
+__global__ __launch_bounds__(kGT) void update_gemm_large_kernel(float* c, int64_t ldc, const float* a, const float* b,
+                                                                int rows, int64_t rest, int n) {
+  __shared__ __align__(16) float as[kGK][kLB];
+  __shared__ __align__(16) float bs[kGK][kLB];
+  const int64_t r0 = static_cast<int64_t>(blockIdx.y) * kLB;
+  const int x0 = blockIdx.x * kLB;
+  const int tid = threadIdx.x;
+  const int tr = (tid / 16) * 4, tx = (tid % 16) * 4;
+  const int lj = tid % kLB, lk = tid / kLB;  // loads: column lj of K rows lk, lk + 2, ..
+  constexpr int kLoads = kGK * kLB / kGT;    // 8 per operand
+  const bool rin = r0 + lj < rest, xin = x0 + lj < n;
+  const float* ap = a + r0 + lj;
+  const float* bp = b + x0 + lj;
+  float ra[kLoads], rb[kLoads];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int k = k0 + lk + 2 * i;
+      ra[i] = (k < rows && rin) ? ap[static_cast<int64_t>(k) * rest] : 0.f;
+      rb[i] = (k < rows && xin) ? bp[static_cast<int64_t>(k) * n] : 0.f;
+    }
+  };
+  float acc[8][8] = {};
+  fetch(0);
+  for (int k0 = 0; k0 < rows; k0 += kGK) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      as[lk + 2 * i][lj] = ra[i];
+      bs[lk + 2 * i][lj] = rb[i];
+    }
+    __syncthreads();
+    if (k0 + kGK < rows) fetch(k0 + kGK);
+#pragma unroll
+    for (int kk = 0; kk < kGK; ++kk) {
+      float av[8], bv[8];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4 qa = *reinterpret_cast<const float4*>(&as[kk][tr + 64 * h]);
+        const float4 qb = *reinterpret_cast<const float4*>(&bs[kk][tx + 64 * h]);
+        av[4 * h] = qa.x, av[4 * h + 1] = qa.y, av[4 * h + 2] = qa.z, av[4 * h + 3] = qa.w;
+        bv[4 * h] = qb.x, bv[4 * h + 1] = qb.y, bv[4 * h + 2] = qb.z, bv[4 * h + 3] = qb.w;
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+    }
+    __syncthreads();
+  }
+  const bool vec = n % 4 == 0 && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(c) % 16 == 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int64_t r = r0 + tr + (i & 3) + 64 * (i >> 2);
+    if (r >= rest) continue;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int x = x0 + tx + 64 * h;
+      float* p = c + r * ldc + x;
+      if (vec && x < n) {
+        float4 q = *reinterpret_cast<float4*>(p);
+        q.x -= acc[i][4 * h], q.y -= acc[i][4 * h + 1], q.z -= acc[i][4 * h + 2], q.w -= acc[i][4 * h + 3];
+        *reinterpret_cast<float4*>(p) = q;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (x + j < n) p[j] -= acc[i][4 * h + j];
+      }
+    }
   }
 }
 
@@ -273,8 +364,15 @@ hipError_t optq_chunk_factor(const double* u, const double* v, int64_t ld, int64
 hipError_t optq_update(float* w_rest, int64_t ldw, const float* m, const float* e, int rows, int64_t rest, int n,
                        hipStream_t s) {
   if (rest <= 0) return hipSuccess;
-  const dim3 grid(blocks_for(n, kGB), static_cast<unsigned>((rest + kGB - 1) / kGB));
-  hipLaunchKernelGGL(update_gemm_kernel, grid, dim3(kGT), 0, s, w_rest, ldw, m, e, rows, rest, n);
+  // the large tiles where they fill the chip's 256 compute units, the small ones below that
+  const int64_t tiles = static_cast<int64_t>(blocks_for(n, kLB)) * blocks_for(rest, kLB);
+  if (tiles >= 256) {
+    const dim3 grid(blocks_for(n, kLB), blocks_for(rest, kLB));
+    hipLaunchKernelGGL(update_gemm_large_kernel, grid, dim3(kGT), 0, s, w_rest, ldw, m, e, rows, rest, n);
+  } else {
+    const dim3 grid(blocks_for(n, kGB), static_cast<unsigned>((rest + kGB - 1) / kGB));
+    hipLaunchKernelGGL(update_gemm_kernel, grid, dim3(kGT), 0, s, w_rest, ldw, m, e, rows, rest, n);
+  }
   return hipGetLastError();
 }
 
