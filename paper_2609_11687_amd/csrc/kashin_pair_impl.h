@@ -337,6 +337,7 @@ struct Cfg {
   // three-pass path (N = R0 M R0, one butterfly of the outer passes per thread)
   static constexpr bool RES = NP == 3 && rad[0] == rad[NP - 1] && R0 % 2 == 0 && B0 == 1;
   static constexpr int M = RES ? rad[1] : 1;
+  static constexpr bool UNI = RES && M == R0 && (R0 & (R0 - 1)) == 0;  // one power-of-two radix throughout
   static constexpr int S1 = NB0 + (R0 == 8 ? 4 : 2);   // row strides of the two exchange layouts (below)
   static constexpr int S2 = NB0 + (R0 == 20 ? 8 : 1);
   static constexpr int LDS = RES ? R0 * (S1 > S2 ? S1 : S2) + 2 : N + (N >> PS) + 4;
@@ -395,12 +396,23 @@ __device__ __forceinline__ float lane63(float v) {
 }
 
 // Sum over the wave in a fixed order: quad xor 1, 2, half-row mirror, row mirror, then the
-// row sums folded into lane 63 by row broadcasts; returned as a wave-uniform value.
+// row sums folded into lane 63 by row broadcasts; returned as a wave-uniform value.  With ALT the
+// lanes of a row fold in the order xor 2, 4, 8, 1 (lane 15 of a row rotated by 4 and 8 adds exactly
+// those pairs): the order of the uniform shapes (N = 512 and 4096), whose step sizes, and so whose
+// codes, stay those of earlier builds bit for bit.
+template <bool ALT = false>
 __device__ __forceinline__ float wave_sum(float v) {
-  v += dpp<0xb1>(v);       // quad_perm [1,0,3,2]
-  v += dpp<0x4e>(v);       // quad_perm [2,3,0,1]
-  v += dpp<0x141>(v);      // row_half_mirror
-  v += dpp<0x140>(v);      // row_mirror
+  if constexpr (ALT) {
+    v += dpp<0x4e>(v);   // quad_perm [2,3,0,1]
+    v += dpp<0x124>(v);  // row_ror:4
+    v += dpp<0x128>(v);  // row_ror:8
+    v += dpp<0xb1>(v);   // quad_perm [1,0,3,2]
+  } else {
+    v += dpp<0xb1>(v);   // quad_perm [1,0,3,2]
+    v += dpp<0x4e>(v);   // quad_perm [2,3,0,1]
+    v += dpp<0x141>(v);  // row_half_mirror
+    v += dpp<0x140>(v);  // row_mirror
+  }
   v += dpp<0x142, 0xa>(v); // row_bcast:15 into rows 1 and 3
   v += dpp<0x143, 0xc>(v); // row_bcast:31 into rows 2 and 3
   return lane63(v);
@@ -418,10 +430,10 @@ __device__ __forceinline__ float wave_max(float v) {
 // Sum of K values over the workgroup in a fixed order (every thread gets the same bits).
 // `red` holds 2 * NW * 32 floats; consecutive calls alternate halves, so one barrier per
 // call suffices.
-template <int T, int K>
+template <int T, int K, bool ALT = false>
 __device__ __forceinline__ void block_sum(float (&v)[K], float* red, int& slot) {
 #pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
+  for (int k = 0; k < K; ++k) v[k] = wave_sum<ALT>(v[k]);
   if constexpr (T > 64) {
     constexpr int NW = (T + 63) / 64;
     float* r = red + (slot & 1) * (NW * 32);
@@ -1139,7 +1151,7 @@ __device__ __forceinline__ float2 greedy_step(float2 (&z)[C::E], float2 (&acc)[C
     s[0] += fabsf(z[e].x);
     s[1] += fabsf(z[e].y);
   }
-  block_sum<C::T, 2>(s, red, slot);
+  block_sum<C::T, 2, C::UNI>(s, red, slot);
   const float ca = div_n<C::N>(s[0]);
   const float cb = div_n<C::N>(s[1]);
   if (trace != nullptr) {
@@ -1300,18 +1312,20 @@ __device__ __forceinline__ void sub_from_rows(float2 (&z)[C::E], const void* w, 
 template <class C>
 __device__ __forceinline__ void normalise_pair(float2 (&z)[C::E], float* red, int& slot, float2& scale,
                                                float2& unscale, bool& bad_a, bool& bad_b) {
-  float mx[2] = {0.f, 0.f};
-  float nf[2] = {0.f, 0.f};
+  // largest magnitude by its bits (the order of the floats, NaN above infinity): two instructions an
+  // entry where a finiteness test, a select and a maximum took six, a tenth of a P-only pair's VALU
+  uint32_t ma = 0, mb = 0;
 #pragma unroll
   for (int e = 0; e < C::E; ++e) {
-    const float ax = fabsf(z[e].x), ay = fabsf(z[e].y);
-    if (ax <= FLT_MAX) mx[0] = fmaxf(mx[0], ax); else nf[0] = 1.f;
-    if (ay <= FLT_MAX) mx[1] = fmaxf(mx[1], ay); else nf[1] = 1.f;
+    const uint32_t ba = __float_as_uint(z[e].x) & 0x7fffffffu, bb = __float_as_uint(z[e].y) & 0x7fffffffu;
+    ma = ma > ba ? ma : ba;
+    mb = mb > bb ? mb : bb;
   }
-  float v[4] = {mx[0], mx[1], nf[0], nf[1]};
-  block_max<C::T, 4>(v, red, slot);
-  bad_a = v[2] != 0.f;
-  bad_b = v[3] != 0.f;
+  constexpr uint32_t kInf = 0x7f800000u;
+  float v[2] = {__uint_as_float(ma < kInf ? ma : kInf), __uint_as_float(mb < kInf ? mb : kInf)};
+  block_max<C::T, 2>(v, red, slot);
+  bad_a = v[0] > FLT_MAX;
+  bad_b = v[1] > FLT_MAX;
   int ea = 0, eb = 0;
   if (!bad_a && v[0] > 0.f) (void)frexpf(v[0], &ea);
   if (!bad_b && v[1] > 0.f) (void)frexpf(v[1], &eb);
@@ -1321,10 +1335,17 @@ __device__ __forceinline__ void normalise_pair(float2 (&z)[C::E], float* red, in
   eb = eb < -126 ? -126 : eb;
   scale = make_float2(ldexpf(1.f, -ea), ldexpf(1.f, -eb));
   unscale = make_float2(ldexpf(1.f, ea), ldexpf(1.f, eb));
+  if (bad_a || bad_b) {  // uniform over the workgroup
+#pragma unroll
+    for (int e = 0; e < C::E; ++e) {
+      z[e].x = bad_a ? 0.f : z[e].x;
+      z[e].y = bad_b ? 0.f : z[e].y;
+    }
+  }
 #pragma unroll
   for (int e = 0; e < C::E; ++e) {
-    z[e].x = bad_a ? 0.f : z[e].x * scale.x;
-    z[e].y = bad_b ? 0.f : z[e].y * scale.y;
+    z[e].x *= scale.x;
+    z[e].y *= scale.y;
   }
 }
 
@@ -1397,7 +1418,7 @@ __device__ __forceinline__ void cluster_factor(const float2 (&x)[C::E], float2 c
         });
         float acc[8] = {s0, s1, s2, s3, static_cast<float>(cnt & 255u), static_cast<float>((cnt >> 8) & 255u),
                         static_cast<float>((cnt >> 16) & 255u), static_cast<float>(cnt >> 24)};
-        block_sum<C::T, 8>(acc, red, slot);
+        block_sum<C::T, 8, C::UNI>(acc, red, slot);
 #pragma unroll
         for (int c = 0; c < 4; ++c)
           if (acc[4 + c] > 0.f) q[sd][c] = acc[c] / acc[4 + c];
@@ -1782,12 +1803,15 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
     float2 scale, unscale;
     bool bad_a, bad_b;
     normalise_pair<C>(z, red, slot, scale, unscale, bad_a, bad_b);
+    // a row that is not finite is zero in the pair and becomes NaN by its factor
+    unscale.x = bad_a ? qnan : unscale.x;
+    unscale.y = bad_b ? qnan : unscale.y;
     if constexpr (RES) apply_P_res<C>(z, lds, rr);
     else apply_P<C>(z, lds, a.tw, a.mid4);
     if (!recon) {
       for_each_elem<C>([&](int e, int i) {
-        a.y[ra * a.ldy + i] = bad_a ? qnan : z[e].x * unscale.x;
-        if (rb >= 0) a.y[rb * a.ldy + i] = bad_b ? qnan : z[e].y * unscale.y;
+        a.y[ra * a.ldy + i] = z[e].x * unscale.x;
+        if (rb >= 0) a.y[rb * a.ldy + i] = z[e].y * unscale.y;
       }, tid);
       lds_barrier();  // the last pass read the buffer the next item's first pass writes
       continue;
@@ -1798,7 +1822,7 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
       constexpr int B = rot_odd_part(N);
       lds_barrier();  // the last pass read the buffer
       for_each_elem<C>([&](int e, int i) {
-        lds[i] = make_float2(bad_a ? qnan : z[e].x * unscale.x, bad_b ? qnan : z[e].y * unscale.y);
+        lds[i] = make_float2(z[e].x * unscale.x, z[e].y * unscale.y);
       }, tid);
       lds_barrier();
       const uint8_t* cua = static_cast<const uint8_t*>(a.w) + ra * NBY;
@@ -1833,8 +1857,8 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
     }
     lds_barrier();  // the last pass read the buffer the outputs are staged in
     for_each_elem<C>([&](int e, int i) {
-      lf[i] = bad_a ? qnan : z[e].x * unscale.x;
-      lf[N + i] = bad_b ? qnan : z[e].y * unscale.y;
+      lf[i] = z[e].x * unscale.x;
+      lf[N + i] = z[e].y * unscale.y;
     }, tid);
     lds_barrier();
     // 2. reconstruction: w_hat = P v_q + u_q in row order, 16-byte stores
@@ -1934,29 +1958,21 @@ __device__ __forceinline__ void store_pair_staged(float2* lds, float* out_a, flo
 // With a.rows set, workgroup i decomposes the pair holding row a.rows[i] and records that
 // row's signs, step sizes, choices and ||rho||^2 after every step.
 //
-// Where the workgroup shape caps the registers (more than 512 threads: one workgroup per CU,
-// 168 or 128 VGPRs) the four arrays do not fit; vhat then lives in private memory between its
-// steps (16-byte loads and stores of the whole array at each vhat-step), so that rho, z and the
-// transform's array stay in registers.
+// Where the workgroup shape caps the registers (more than 512 threads: one workgroup per CU, 168
+// VGPRs) or an array has 32 complex values, the arrays do not fit; vhat then lives in private memory
+// between its steps (16-byte loads and stores of the whole array at each vhat-step), so that the
+// residual's two domains and the transform's array stay in registers.
 template <class C>
 constexpr bool sched_vh_in_memory() {
   return (C::T > 512 || C::E >= 32) && C::E % 2 == 0;
 }
-// With a 128-register budget (1024 threads), and on the five-pass shape with 64 values per array
-// (N = 13824), the stepped values wait in private memory too while P runs, so that only the
-// transformed array occupies registers across the transform (the compiler otherwise spills
-// inside the loop there).
-template <class C>
-constexpr bool sched_park() {
-  return sched_vh_in_memory<C>() && ((C::T > 512 && C::W >= 4) || (C::E >= 32 && C::NP >= 5));
-}
-// Where LDS has room beside the transform's buffer (N = 10000, 11008: one element per butterfly
-// thread, B0 = 1), vhat lives there instead, as many of each thread's 2E values as fit (row a's
-// first, then row b's; each thread its own slots, read and written only at vhat-steps), the rest
-// in registers: private memory would be written back to HBM at every vhat-step.
+// Where LDS has room beside the transform's buffer (N = 11008: one element per butterfly thread,
+// B0 = 1), vhat lives there instead, as many of each thread's 2E values as fit (row a's first, then
+// row b's; each thread its own slots, read and written only at vhat-steps), the rest in registers:
+// private memory would be written back to HBM at every vhat-step.
 template <class C>
 constexpr int sched_vh_lds_values() {
-  if constexpr (!sched_vh_in_memory<C>() || sched_park<C>() || C::B0 != 1) {
+  if constexpr (!sched_vh_in_memory<C>() || C::B0 != 1) {
     return 0;
   } else {
     constexpr int used = (C::LDS + small_tw_total<C>()) * 8 + 2 * C::NW * 32 * 4;
@@ -2006,8 +2022,6 @@ pair_schedule_kernel(KArgs a, int64_t item0) {
   const int vt = threadIdx.x;
   const bool vown = vt < C::NB0;  // threads past the last butterfly hold no elements
   auto vh_slot = [&](int sl) -> float& { return vhl[sl * C::NB0 + vt]; };
-  constexpr bool PARK = sched_park<C>();
-  float4 park[PARK ? C::E / 2 : 1];  // the stepped values across P (PARK)
   load_pair<C>(sv, a.w, a.dtype, a.ldw, ra, rb);
   float2 scale, unscale;
   bool bad_a, bad_b;
@@ -2056,7 +2070,7 @@ pair_schedule_kernel(KArgs a, int64_t item0) {
       s12[11] += y[e].y * y[e].y;
     }
     if constexpr (C::NW * 12 > 64) block_sum_lanes<C::T, 12>(s12, red, slot);
-    else block_sum<C::T, 12>(s12, red, slot);
+    else block_sum<C::T, 12, C::UNI>(s12, red, slot);
     // threads past the last butterfly hold zeros: they add nothing to the counts above
     // v: l1 of rho and z, nonzero counts of rho and z, ||rho||^2 (rows a, b in turn)
     const float v[10] = {za ? s12[2] : s12[0],  zb ? s12[3] : s12[1], za ? s12[0] : s12[2], zb ? s12[1] : s12[3],
@@ -2154,22 +2168,7 @@ pair_schedule_kernel(KArgs a, int64_t item0) {
       sv[e] = make_float2(xa, xb);
       y[e] = sv[e];
     }
-    if constexpr (PARK) {
-      const int b = opaque(0);
-#pragma unroll
-      for (int h = 0; h < C::E / 2; ++h)
-        park[b + h] = make_float4(sv[2 * h].x, sv[2 * h].y, sv[2 * h + 1].x, sv[2 * h + 1].y);
-    }
     applyP(y);  // the other domain of each row
-    if constexpr (PARK) {
-      const int b = opaque(0);
-#pragma unroll
-      for (int h = 0; h < C::E / 2; ++h) {
-        const float4 q = park[b + h];
-        sv[2 * h] = make_float2(q.x, q.y);
-        sv[2 * h + 1] = make_float2(q.z, q.w);
-      }
-    }
     za = va;
     zb = vb;
     if constexpr (tracing) {
@@ -2180,7 +2179,7 @@ pair_schedule_kernel(KArgs a, int64_t item0) {
         const float2 rv = zs ? y[e] : sv[e];
         q[0] += side ? rv.y * rv.y : rv.x * rv.x;
       }
-      block_sum<C::T, 1>(q, red, slot);
+      block_sum<C::T, 1, C::UNI>(q, red, slot);
       if (threadIdx.x == 0) a.tr_r2[item * steps + st] = q[0] * unsel * unsel;
     }
   }
@@ -2227,6 +2226,7 @@ pair_schedule_kernel(KArgs a, int64_t item0) {
   };
 #pragma unroll
   for (int e = 0; e < C::E; ++e) y[e] = vhat_at(e);
+  lds_barrier();  // without an r output nothing else separates the last step's P from this one
   applyP(y);
   out_rows(a.u, pa, pb);
   store_pair_staged<C>(lds, pa, pb, [&](int e) {
