@@ -843,7 +843,8 @@ def main() -> int:
     else:
         achieved = dom_bytes / dom_s / 1e9
         kname = f"rotate_kernel[b={dom_n // (dom_n & -dom_n)}]" if main_kind == "rotate" else "pair_pmap_kernel"
-        grid = (lambda l: l.rows) if main_kind == "rotate" else (
+        # rows up to 4096 long are walked by at most 2048 resident workgroups, longer ones take one each
+        grid = (lambda l: min(l.rows, 2048) if l.n <= 4096 else l.rows) if main_kind == "rotate" else (
             lambda l: l.wgs or min((l.rows + 1) // 2, PMAP_GRID))
         keyn = (lambda l: 0) if main_kind == "rotate" else (lambda l: l.n)  # the rotation kernel takes n at run time
         roofline = {

@@ -28,13 +28,14 @@ COPY_BYTES = 256 << 20  # the calibration copy reads and writes 256 MiB
 
 
 def _short(name: str) -> tuple[str, int]:
-    m = re.search(r"(pair_greedy_kernel|pair_pmap_kernel|pair_schedule_kernel|rotate_kernel|cluster_kernel|"
+    m = re.search(r"(pair_greedy_kernel|pair_pmap_kernel|pair_schedule_kernel|rotate_kernel|rotate_long_kernel|"
+                  r"cluster_kernel|update_gemm\w*|"
                   r"__amd_rocclr_copyBuffer\w*|elementwise_kernel|potf2\w*|\w*substitution\w*|Cijk_\w*)", name)
     c = re.search(r"Cfg<(\d+)", name)
     base = m.group(1) if m else name[:40]
     if base.startswith("Cijk_"):  # library GEMM: operand layout, type and macro tile
         base = base[:42]
-    rot = re.search(r"rotate_kernel<(\d+), (true|false)", name)  # rotate_kernel<odd factor, inverse, input type>
+    rot = re.search(r"rotate(?:_long)?_kernel<(\d+), (true|false)", name)  # rotate_kernel<odd factor, inverse, input type>
     if rot:
         base += f"[b={rot.group(1)}" + (",inverse]" if rot.group(2) == "true" else "]")
     # pair_greedy_kernel<Cfg, LLOYD, QUANT, ROT>

@@ -1,0 +1,86 @@
+"""GPU tests at the edges of kernel variants: rows walked by resident workgroups in the rotation,
+and the two tile sizes of the compensation's trailing update."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle.kashin_ref as ref
+import parity_util as pu
+from paper_2609_11687_amd import kashin as K
+
+pytestmark = pytest.mark.gpu
+
+
+# n at and around the element counts per thread that are compiled (1, 4, 8, 12, 16 times 256 entries),
+# the padded and unpadded layouts, every odd part; m above and below the resident workgroups
+# (at most 2048), so that workgroups take no, one or several rows
+@pytest.mark.parametrize("n,m", [(1, 3), (3, 5), (43, 4), (128, 2100), (256, 4500), (384, 2049), (512, 2047), (1024, 2100),
+                                 (1376, 70), (1536, 2051), (2048, 2050), (3072, 2500), (4096, 2305), (6144, 2000),
+                                 (8192, 1100), (11008, 800), (16384, 520)])
+@pytest.mark.parametrize("inverse", [False, True])
+def test_rotate_rows_equal_single_rows(n, m, inverse):
+    """Every row of a call over many rows equals the row rotated alone, bit for bit (also in place
+    and with spare entries between the rows), and sampled rows agree with the oracle."""
+    print(f"rotate n={n} m={m} inverse={inverse}", flush=True)
+    rng = np.random.default_rng(n + m)
+    x = rng.standard_normal((m, n)).astype(np.float32)
+    xd = pu.to_dev(x)
+    y = torch.empty_like(xd)
+    K.kashin_rotate(n, 9, xd, y, inverse=inverse)
+    wide = torch.zeros((m, n + 3), device="cuda")
+    wide[:, :n] = xd
+    K.kashin_rotate(n, 9, wide[:, :n], wide[:, :n], inverse=inverse)
+    picks = sorted({0, 1, m // 2, m - 2, m - 1, min(m - 1, 2048)})
+    alone = torch.empty((len(picks), n), device="cuda")
+    for i, r in enumerate(picks):
+        K.kashin_rotate(n, 9, xd[r:r + 1], alone[i:i + 1], inverse=inverse)
+    torch.cuda.synchronize()
+    assert torch.equal(wide[:, :n], y)
+    assert torch.equal(wide[:, n:], torch.zeros((m, 3), device="cuda"))
+    assert torch.equal(alone, y[picks])
+    want = ref.rotate(x[picks].astype(np.float64), 9, inverse=inverse)
+    got = y[picks].cpu().numpy()
+    # each output is a sum of n terms through at most 14 additions and 43 products of the odd factor:
+    # well below 64 roundings of 2^-24 of the row's largest entries
+    assert np.abs(got - want).max() <= 64 * 2.0 ** -24 * max(np.abs(want).max(), np.abs(x).max())
+
+
+@pytest.mark.parametrize("n,d_in,chunk", [(11008, 500, 100), (4096, 1200, 128), (4096, 1129, 33), (10000, 520, 1)])
+def test_update_tiles(n, d_in, chunk):
+    """The trailing update after one chunk against float64, at sizes with ragged tiles that take the
+    128 x 128 tiles (at least 256 of them), and its first columns bit for bit against a call whose
+    remainder takes the 64 x 64 tiles."""
+    print(f"update n={n} d_in={d_in} chunk={chunk}", flush=True)
+    rest = d_in - chunk
+    tiles = lambda r: -(-n // 128) * -(-r // 128)  # noqa: E731
+    assert tiles(rest) >= 256 and tiles(60) < 256
+    g = torch.Generator(device="cuda").manual_seed(n + chunk)
+    plan = K.kashin_plan(n, 5, 3)
+    w = torch.randn((d_in, n), generator=g, device="cuda") * 0.02
+    h = torch.randn((2 * d_in, d_in), generator=g, device="cuda")
+    u, v = (torch.empty((d_in, d_in), dtype=torch.float64, device="cuda") for _ in range(2))
+    K.kashin_optq_factor((h.t().contiguous() @ h) / (2 * d_in), u, v)
+
+    def step(d):
+        wt = w[:d].clone()
+        nb = (n + 3) // 4
+        cu, cv = (torch.empty((chunk, nb), dtype=torch.uint8, device="cuda") for _ in range(2))
+        ce = torch.empty((chunk, 2, 4), device="cuda")
+        q = torch.empty((chunk, n), device="cuda")
+        work = torch.empty(K.kashin_optq_workspace_bytes(d, n, chunk), dtype=torch.uint8, device="cuda")
+        K.kashin_optq_quantize(plan, wt, u[:d, :d], v[:d, :d], chunk, False, 0, cu, cv, ce, q, work,
+                               quantize_rows=chunk)
+        torch.cuda.synchronize()
+        return wt, q
+
+    wt, q = step(d_in)
+    small, q2 = step(chunk + 60)
+    assert torch.equal(q, q2)
+    assert torch.equal(small, wt[:chunk + 60])
+    delta = (w[:chunk] - q).double()
+    m = (v[:chunk, :chunk] @ u[:chunk, chunk:]).t().contiguous()
+    want = w[chunk:].double() - m @ delta
+    # each term rounded once in Delta and M, `chunk` FMAs, one subtraction
+    bound = 2.0 ** -24 * ((chunk + 3) * (m.abs() @ delta.abs()) + w[chunk:].abs().double() + want.abs()) + 1e-30
+    assert bool(((wt[chunk:].double() - want).abs() <= bound).all())
