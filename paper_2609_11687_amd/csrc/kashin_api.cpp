@@ -75,9 +75,9 @@ void make_signs(int32_t n, uint64_t seed, int8_t* out) {
 //       inverse passes 1..np-1 (radices in reverse order) -- entry [jm][r] =
 //       exp(-2 pi i r jm / (NS R)), each table padded to an even length;
 //  mid: for the first inverse pass (radix R = last forward radix, stride 1), entry j R + r
-//       for element k = j + r n/R: Y'_k = f_k Y_s(k) with s(k) = k and f_k = eps_k / n when
+//       for element k = j + r n/R: Y'_k = f_k Y_s(k) with s(k) = k and f_k = eps_k / D when
 //       eps_k == eps_{n-k} (k = 0 and k = n/2 pair with themselves), else s(k) = n - k and
-//       f_k = eps_k exp(i pi k / n) / n; stored as {Re f, Im f, LDS byte address of s(k), eps_k}.
+//       f_k = eps_k exp(i pi k / n) / D (D = n, or p_divisor); stored as {Re f, Im f, LDS byte address of s(k), eps_k}.
 void build_tables(int n, const int8_t* eps, std::vector<float2>* tw, std::vector<float4>* mid) {
   kashin::PlanShape sh;
   kashin::plan_shape(n, &sh);
@@ -102,6 +102,7 @@ void build_tables(int n, const int8_t* eps, std::vector<float2>* tw, std::vector
   }
   const int R = sh.rad[sh.np - 1];
   const int nb = n / R;
+  const double div = kashin::p_divisor(n, sh.rad[0], sh.np == 3 ? sh.rad[1] : 1);
   mid->assign(n, make_float4(0.f, 0.f, 0.f, 0.f));
   for (int j = 0; j < nb; ++j)
     for (int r = 0; r < R; ++r) {
@@ -111,13 +112,13 @@ void build_tables(int n, const int8_t* eps, std::vector<float2>* tw, std::vector
       float fx, fy;
       int src;
       if (eps[k] == eps[partner]) {
-        fx = float(ek / n);
+        fx = float(ek / div);
         fy = 0.f;
         src = k;
       } else {
         const double ang = pi * double(k) / double(n);
-        fx = float(ek * std::cos(ang) / n);
-        fy = float(ek * std::sin(ang) / n);
+        fx = float(ek * std::cos(ang) / div);
+        fy = float(ek * std::sin(ang) / div);
         src = partner;
       }
       const int addr = kashin::pad_slot(n, src) * int(sizeof(float2));

@@ -120,6 +120,41 @@ struct PlanShape {
 };
 bool plan_shape(int n, PlanShape* out);
 
+// Relative error of the factor m (1, t) by which a butterfly multiplies for e^{i pi a / 16}, a = 1..4
+// (the larger of cosine and sine, and their ratio, both rounded to float), along the true value.
+constexpr double twiddle_gain(int a) {
+  constexpr double c[5] = {1.0, 0.98078528040323044913, 0.92387953251128675613, 0.83146961230254523708,
+                           0.70710678118654752440};
+  constexpr double s[5] = {0.0, 0.19509032201612826785, 0.38268343236508977173, 0.55557023301960222474,
+                           0.70710678118654752440};
+  const double m = static_cast<double>(static_cast<float>(c[a]));
+  const double t = static_cast<double>(static_cast<float>(s[a] / c[a]));
+  return m * (c[a] + t * s[a]) - 1.0;
+}
+// Relative gain of the in-register transform of length r (its power-of-two part, radix 2): every one of
+// these constants rounds down, so that each stage shrinks the half of its energy that goes through its
+// twiddles: -1.4e-8 for 16, -2.5e-8 for 32.
+constexpr double dft_gain(int r) {
+  r &= -r;
+  double g = 0.0;
+  for (int len = 8; len <= r; len *= 2) {
+    double sum = 0.0;
+    for (int j = 0; j < len / 2; ++j) {
+      const int k = (j * (32 / len)) % 8;
+      sum += twiddle_gain(k <= 4 ? k : 8 - k);
+    }
+    g += 0.5 * sum / (len / 2);
+  }
+  return g;
+}
+// The divisor of P's frequency factors for n = r0 m r0: n, times the transforms' gain for the lengths
+// above 4096 (without the correction the two radix-32 passes of a transform put 1.1e-7 to 1.3e-7 of
+// P's 2.2e-7 rms error into a plain factor).  Below, and with a split pass, P is as exact as it was
+// before the three-pass path and its results keep their bits.
+constexpr double p_divisor(int n, int r0, int m) {
+  return (n > 4096 && m <= 32) ? n * (1.0 + 2.0 * (2.0 * dft_gain(r0) + dft_gain(m))) : n;
+}
+
 // LDS layout of the generic path's transform buffer: element i of a length-n vector lives at float2
 // slot i + (i >> pad_shift(n)).
 __host__ __device__ constexpr int pad_shift(int n) { return n % 512 == 0 ? 5 : 4; }

@@ -704,9 +704,9 @@ constexpr int small_tw_total() {
 
 // eps factors f_k of the fused step for the thread's elements k = t + q N/R0: kept as R0 complex
 // values, or -- COMPACT, for kernels whose block loop is register-bound (the split shape, radices
-// above 16, a 128-register budget) -- as e^{i pi t/N}/N and two masks (bit q: eps_k < 0, and
-// eps_k != eps_{N-k}), from which f_k = eps_k / N or eps_k e^{i pi k/N} / N =
-// eps_k (e^{i pi t/N} / N) e^{i pi q/R0} is rebuilt at each use.
+// above 16, a 128-register budget) -- as e^{i pi t/N}/D and two masks (bit q: eps_k < 0, and
+// eps_k != eps_{N-k}), from which f_k = eps_k / D or eps_k e^{i pi k/N} / D =
+// eps_k (e^{i pi t/N} / D) e^{i pi q/R0} is rebuilt at each use (D = N, or p_divisor).
 template <class C>
 constexpr bool compact_eps() {
   return has_split_pass<C>() || C::R0 > 16 || (C::W >= 4 && C::R0 == 16);
@@ -727,7 +727,7 @@ __device__ __forceinline__ float2 eps_factor(const EpsRegs<C, COMPACT>& e, bool&
     partner = (e.swap >> q) & 1u;
     const bool neg = (e.neg >> q) & 1u;
     constexpr float cx = HalfTab<C::R0>::c[q], cy = HalfTab<C::R0>::s[q];
-    constexpr float inv_n = static_cast<float>(1.0 / C::N);
+    constexpr float inv_n = static_cast<float>(1.0 / p_divisor(C::N, C::R0, C::M));
     const float2 g = partner ? make_float2(e.base.x * cx - e.base.y * cy, e.base.x * cy + e.base.y * cx)
                              : make_float2(inv_n, 0.f);
     return neg ? make_float2(-g.x, -g.y) : g;
@@ -740,7 +740,7 @@ __device__ __forceinline__ float2 eps_factor(const EpsRegs<C, COMPACT>& e, bool&
 
 template <class C, bool COMPACT = false>
 struct ResRegs {
-  static constexpr bool compact = COMPACT && C::R0 == 16;
+  static constexpr bool compact = COMPACT && has_split_pass<C>();
   float2 tw[C::R0];         // stored powers of w_N^t (kept_tw); the rest are products of two of these
   EpsRegs<C, COMPACT> eps;  // eps factors of the fused step for elements k = t + r N/R0
 };
@@ -749,7 +749,10 @@ __device__ __forceinline__ float2 cmulf(float2 x, float2 y) {
   return make_float2(x.x * y.x - x.y * y.y, x.x * y.y + x.y * y.x);
 }
 // Twiddle r of the last pass, w_N^{r t}: below radix 16 all are kept; else r = 4a + b is the product
-// w_{4a} w_b (one rounding) of the kept powers 1, 2, 3, 4, 8, 12, ..; compact keeps only 1 and 4.
+// w_{4a} w_b (one rounding) of the kept powers 1, 2, 3, 4, 8, 12, ..  Only the split shape keeps no
+// more than 1 and 4, from which w^15 takes five products: at 5120 and 6144 that put P's error up by
+// 10 and 7 % (rms 18.9e-8 and 19.5e-8 of the input against 17.0e-8 and 18.1e-8), for 0.2 and 1.2 % of
+// the quantiser's time (the four more powers spill 27 and 22 registers).
 template <class C, class RR>
 constexpr bool kept_tw(int r) {
   return C::R0 < 16 ? r > 0 : (RR::compact ? (r == 1 || r == 4) : r > 0 && (r < 4 || r % 4 == 0));
@@ -810,7 +813,8 @@ __device__ __forceinline__ void resident_load(RR& rr, float2* lds, const float2*
     sincospif(static_cast<float>(tl) / static_cast<float>(C::N), &sn, &cs);
     rr.eps.neg = neg;
     rr.eps.swap = swap;
-    rr.eps.base = make_float2(cs * static_cast<float>(1.0 / C::N), sn * static_cast<float>(1.0 / C::N));
+    constexpr float inv_n = static_cast<float>(1.0 / p_divisor(C::N, C::R0, C::M));
+    rr.eps.base = make_float2(cs * inv_n, sn * inv_n);
   } else {
     sfor<0, R>([&](auto rv) {
       const float4 m = mid[tl * R + decltype(rv)::value];
@@ -855,7 +859,9 @@ __device__ __forceinline__ void res_inner_pass(float2* __restrict__ lds) {
   float2 a[BPT][M];
   constexpr int MP = (M + 1) / 2;
   // twiddle pairs read before the barrier, so that their latency passes while the waves gather there
-  constexpr int PF = BPT == 1 ? (MP < 8 ? MP : 8) : 0;
+  // (eight of them; four where 128 registers hold everything: y = P x at 6144 117 -> 106 us a 5461 rows)
+  constexpr int PFM = C::W >= 4 && C::R0 >= 16 ? 4 : 8;
+  constexpr int PF = BPT == 1 ? (MP < PFM ? MP : PFM) : 0;
   float4 pf[PF > 0 ? PF : 1];
   sfor<0, BPT>([&](auto iv) {
     constexpr int i = decltype(iv)::value;

@@ -1,7 +1,8 @@
 """GPU tests at the edges of kernel variants: rows walked by resident workgroups in the rotation,
-and the two tile sizes of the compensation's trailing update."""
+the two tile sizes of the compensation's trailing update, and the error of the greedy kernels' own P."""
 import numpy as np
 import pytest
+import scipy.fft
 
 torch = pytest.importorskip("torch")
 
@@ -84,3 +85,35 @@ def test_update_tiles(n, d_in, chunk):
     # each term rounded once in Delta and M, `chunk` FMAs, one subtraction
     bound = 2.0 ** -24 * ((chunk + 3) * (m.abs() @ delta.abs()) + w[chunk:].abs().double() + want.abs()) + 1e-30
     assert bool(((wt[chunk:].double() - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("n", [5120, 6144, 8192, 10000, 13824, 14336, 16384])
+def test_operator_error(n):
+    """P inside the schedule kernel, whose constants are kept in fewer registers than kashin_apply_p's, and
+    P of kashin_apply_p, against float64.  With u = w - r - P vhat formed by the kernel, w - u - r -
+    P64 vhat is P's own error (and three roundings).  An FFT's rms error is c 2^-24 sqrt(log2 n) of its
+    input; these rows through the reverse schedule's first block have c = 0.80 to 0.85 at these lengths,
+    through kashin_apply_p 0.91 to 0.98.  Last-pass twiddles that are chains of products have 0.88 (5120)
+    and 0.90 (6144), radix-32 passes whose constants all round down 0.90 to 0.97 and 1.06 to 1.10."""
+    print(f"operator error n={n}", flush=True)
+    num = den = num_p = den_p = 0.0
+    for seed in (1, 2):
+        w = np.random.default_rng(seed * 100003 + n).standard_normal((64, n)).astype(np.float32)
+        wd = pu.to_dev(w)
+        plan = K.kashin_plan(n, seed, 1)
+        u, v, r, y = (torch.empty_like(wd) for _ in range(4))
+        K.kashin_decompose_schedule(plan, "reverse", wd, u, v, r)
+        K.kashin_apply_p(plan, wd, y)
+        torch.cuda.synchronize()
+        eps = ref.sign_mask(n, seed)
+        p64 = lambda x: scipy.fft.idct(eps * scipy.fft.dct(x, norm="ortho"), norm="ortho")  # noqa: E731
+        w64, u64, v64, r64, y64 = (t.astype(np.float64) for t in (w, *(t.cpu().numpy() for t in (u, v, r, y))))
+        num += ((w64 - u64 - r64 - p64(v64)) ** 2).sum()
+        den += (w64 ** 2).sum()
+        want = p64(w64)
+        num_p += ((y64 - want) ** 2).sum()
+        den_p += (want ** 2).sum()
+    unit = 2.0 ** -24 * np.sqrt(np.log2(n))
+    c, c_p = np.sqrt(num / den) / unit, np.sqrt(num_p / den_p) / unit
+    print(f"c = {c:.3f}, P x {c_p:.3f}", flush=True)
+    assert c <= 0.865 and c_p <= 1.02
