@@ -1235,10 +1235,12 @@ __device__ __forceinline__ void for_each_elem(F&& f, int tid = threadIdx.x) {
 
 // Rows a and b of w (b if >= 0, else zeros) into the LDS buffer in row order as float2 (row a
 // in .x, row b in .y), times the rotation's sign s_i when ROT.  Each thread issues its loads in
-// batches of eight per row before the first store, so that several are in flight at once.
-template <class C, bool ROT, class IT>
-__device__ __forceinline__ void stage_pair_t(float2* lds, const IT* __restrict__ w, int64_t ldw, int64_t ra,
-                                             int64_t rb, uint64_t seed, int tid) {
+// batches of eight per row before the first store, so that several are in flight at once.  Returns the
+// rows (bit 0: a, 1: b) of which the thread saw an entry of at least kRotHuge, where HUGE_ROWS.
+template <class C, bool ROT, bool HUGE_ROWS, class IT>
+__device__ __forceinline__ uint32_t stage_pair_t(float2* lds, const IT* __restrict__ w, int64_t ldw, int64_t ra,
+                                                 int64_t rb, uint64_t seed, int tid) {
+  bool huge_a = false, huge_b = false;
   constexpr int K = (C::N + C::T - 1) / C::T;  // entries per thread and row
   constexpr int BATCH = 8;
   const IT* __restrict__ pa = w + ra * ldw;
@@ -1259,11 +1261,18 @@ __device__ __forceinline__ void stage_pair_t(float2* lds, const IT* __restrict__
       const int i = tid + (k0 + k) * C::T;
       if (k0 + k < K && (C::N % C::T == 0 || i < C::N)) {
         float2 v = make_float2(to_f32(va[k]), rb >= 0 ? to_f32(vb[k]) : 0.f);
-        if constexpr (ROT) v = rv_scale(v, rot_sign(seed, i));
+        if constexpr (ROT) {
+          if constexpr (HUGE_ROWS) {
+            huge_a |= fabsf(v.x) >= kRotHuge;
+            huge_b |= fabsf(v.y) >= kRotHuge;
+          }
+          v = rv_scale(v, rot_sign(seed, i));
+        }
         lds[i] = v;
       }
     }
   }
+  return (huge_a ? 1u : 0u) | (huge_b ? 2u : 0u);
 }
 
 // w (or R w when ROT: the rotation fused into the load) for both rows of the pair, handed to
@@ -1275,15 +1284,23 @@ __device__ __forceinline__ void stage_pair_t(float2* lds, const IT* __restrict__
 template <class C, bool ROT, class F>
 __device__ __forceinline__ void load_pair_staged(const void* w, int dtype, int64_t ldw, int64_t ra, int64_t rb,
                                                  uint64_t seed, float scale, float2* lds, F&& f) {
+  constexpr int B = rot_odd_part(C::N);
+  constexpr bool HUGE_ROWS = ROT && rot_watch_huge<B, false>();
+  __shared__ uint32_t flags[HUGE_ROWS ? C::NW : 1];
   const int tid = threadIdx.x;
+  uint32_t huge = 0;
   lds_barrier();
-  if (dtype == KASHIN_F16) stage_pair_t<C, ROT>(lds, static_cast<const __half*>(w), ldw, ra, rb, seed, tid);
-  else if (dtype == KASHIN_BF16) stage_pair_t<C, ROT>(lds, static_cast<const bf16_t*>(w), ldw, ra, rb, seed, tid);
-  else stage_pair_t<C, ROT>(lds, static_cast<const float*>(w), ldw, ra, rb, seed, tid);
+  if (dtype == KASHIN_F16)
+    huge = stage_pair_t<C, ROT, HUGE_ROWS>(lds, static_cast<const __half*>(w), ldw, ra, rb, seed, tid);
+  else if (dtype == KASHIN_BF16)
+    huge = stage_pair_t<C, ROT, HUGE_ROWS>(lds, static_cast<const bf16_t*>(w), ldw, ra, rb, seed, tid);
+  else huge = stage_pair_t<C, ROT, HUGE_ROWS>(lds, static_cast<const float*>(w), ldw, ra, rb, seed, tid);
+  if constexpr (HUGE_ROWS) rot_note_huge(flags, huge, tid);
   lds_barrier();
   if constexpr (ROT) {
-    constexpr int B = rot_odd_part(C::N);
-    rot_odd_factor_fixed<B, false, C::T, C::N>(lds, tid);
+    huge = 0;
+    if constexpr (HUGE_ROWS) huge = rot_huge_rows<C::NW>(flags);
+    rot_odd_factor_fixed<B, false, C::T, C::N>(lds, huge, tid);
     rot_hadamard<B, C::T>(lds, C::N, tid);
   }
   for_each_elem<C>([&](int e, int i) { f(e, ROT ? rv_scale(lds[i], scale) : lds[i]); }, tid);
@@ -1849,7 +1866,7 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
       }
       lds_barrier();
       rot_hadamard<B, C::T>(lds, N, tid);
-      rot_odd_factor_fixed<B, true, C::T, N>(lds, tid);
+      rot_odd_factor_fixed<B, true, C::T, N>(lds, 0, tid);
       float* ya = a.y + ra * a.ldy;
       float* yb = a.y + (rb >= 0 ? rb : ra) * a.ldy;
       for (int i = tid; i < N; i += C::T) {

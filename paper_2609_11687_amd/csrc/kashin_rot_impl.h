@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "kashin_tables.h"
 
@@ -43,12 +44,47 @@ __device__ __forceinline__ float2 rv_sub(float2 a, float2 b) { return make_float
 __device__ __forceinline__ float rv_scale(float a, float s) { return a * s; }
 __device__ __forceinline__ float2 rv_scale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
 
-// The odd factor C_B by its symmetry m[k][B-1-j] = (-1)^k m[k][j]: with s_j = x_j + x_{B-1-j} and
+// The odd factor C_B, B > 3, by its symmetry m[k][B-1-j] = (-1)^k m[k][j]: with s_j = x_j + x_{B-1-j} and
 // d_j = x_j - x_{B-1-j} (j < H = (B-1)/2), output k of C_B x is sum_j m[k][j] s_j + m[k][H] x_H for even
 // k and sum_j m[k][j] d_j for odd k; outputs j and B-1-j of C_B^T x are E_j +- O_j, the sums over even
-// and odd k.  Half the products of the plain matrix (925 FMAs for B = 43 against 1849).  Every sum
-// runs in ascending order from zero, in the whole-segment and the chunked form alike, so the fused
-// and the standalone rotation agree bit for bit.
+// and odd k.  Half the products of the plain matrix (925 FMAs for B = 43 against 1849).  C_3 is the
+// plain product (its nine FMAs hide behind the LDS accesses).  Every sum runs in ascending order
+// from zero, in the whole-segment and the chunked form alike, so the fused and the standalone
+// rotation agree bit for bit.
+//
+// The pair sums of C_B double their entries and could overflow where the plain product is finite, so a
+// row with an entry of 2^125 or more in magnitude is a quarter of itself inside C_B (a power of two: the
+// same bits otherwise).  Below 2^125 no sum of C_43 can overflow (its rows have l1 norms of at most
+// sqrt(43) < 8); nor, in a quarter row, one whose plain partial sums are all finite.  C_B^T's E_j and O_j
+// are half the sum and the difference of two plain outputs and need no care.
+constexpr float kRotHuge = 0x1p125f;
+template <int B, bool TRANS>
+constexpr bool rot_watch_huge() {
+  return B > 3 && !TRANS;
+}
+
+// Which of up to two rows hold such an entry, one bit each: every wave notes in flags[wave], before the
+// barrier that ends the load, what its threads saw, and reads all NW notes after it (a uniform value).
+__device__ __forceinline__ void rot_note_huge(uint32_t* flags, uint32_t rows, int tid) {
+  const uint32_t w = (__ballot(rows & 1u) ? 1u : 0u) | (__ballot(rows & 2u) ? 2u : 0u);
+  if ((tid & 63) == 0) flags[tid >> 6] = w;
+}
+template <int NW>
+__device__ __forceinline__ uint32_t rot_huge_rows(const uint32_t* flags) {
+  uint32_t w = 0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) w |= flags[i];
+  return __builtin_amdgcn_readfirstlane(w);
+}
+// the noted rows (bit 0: a float's, or .x; bit 1: .y) of the n entries in buf times f, then a barrier
+template <int T, class V>
+__device__ __forceinline__ void rot_scale_rows(V* buf, int n, uint32_t rows, float f, int tid) {
+  for (int i = tid; i < n; i += T) {
+    if constexpr (std::is_same<V, float>::value) buf[i] *= f;
+    else buf[i] = make_float2(buf[i].x * (rows & 1u ? f : 1.f), buf[i].y * (rows & 2u ? f : 1.f));
+  }
+  lds_barrier();
+}
 
 // one segment of length B: v <- C_B v (or C_B^T v), in place, constants compile-time
 template <int B, bool TRANS, class V>
@@ -57,7 +93,15 @@ __device__ __forceinline__ void rot_odd_segment(V* seg) {
   V in[B];
 #pragma unroll
   for (int j = 0; j < B; ++j) in[j] = seg[j];
-  if constexpr (!TRANS) {
+  if constexpr (B <= 3) {
+#pragma unroll
+    for (int k = 0; k < B; ++k) {
+      V acc = rv_zero(in[0]);
+#pragma unroll
+      for (int j = 0; j < B; ++j) acc = rv_fma(TRANS ? DctTab<B>::m[j * B + k] : DctTab<B>::m[k * B + j], in[j], acc);
+      seg[k] = acc;
+    }
+  } else if constexpr (!TRANS) {
 #pragma unroll
     for (int j = 0; j < H; ++j) {
       const V u = in[j], v = in[B - 1 - j];
@@ -90,12 +134,15 @@ __device__ __forceinline__ void rot_odd_segment(V* seg) {
   }
 }
 
-// the odd factor over all n / B segments (one thread per segment), then a barrier
+// the odd factor over all n / B segments (one thread per segment), then a barrier; huge: rot_huge_rows's
+// (0 unless rot_watch_huge)
 template <int B, bool TRANS, int T, class V>
-__device__ __forceinline__ void rot_odd_factor(V* buf, int n, int tid) {
+__device__ __forceinline__ void rot_odd_factor(V* buf, int n, uint32_t huge, int tid) {
   if constexpr (B > 1) {
+    if (huge != 0) rot_scale_rows<T>(buf, n, huge, 0.25f, tid);
     for (int i = tid; i < n / B; i += T) rot_odd_segment<B, TRANS>(buf + i * B);
     lds_barrier();
+    if (huge != 0) rot_scale_rows<T>(buf, n, huge, 4.f, tid);
   }
 }
 
@@ -145,15 +192,16 @@ __device__ __forceinline__ void rot_odd_chunk(const V* seg, V (&acc)[KC]) {
 // computed by NC threads (all inputs read before the barrier, outputs written after it), so that
 // more waves share the work and each holds fewer values; otherwise one thread per segment.
 template <int B, bool TRANS, int T, int N, class V>
-__device__ __forceinline__ void rot_odd_factor_fixed(V* buf, int tid) {
+__device__ __forceinline__ void rot_odd_factor_fixed(V* buf, uint32_t huge, int tid) {
   constexpr int NSEG = N / B;
   constexpr int NC = (B >= 16 && T >= 3 * NSEG) ? 3 : 1;
   if constexpr (NC == 1) {
-    rot_odd_factor<B, TRANS, T>(buf, N, tid);
+    rot_odd_factor<B, TRANS, T>(buf, N, huge, tid);
   } else {
     constexpr int H = (B - 1) / 2;
     constexpr int JC = (H + 1 + NC - 1) / NC;              // output pairs per chunk (TRANS)
     constexpr int KC = TRANS ? 2 * JC : (B + NC - 1) / NC;  // values per chunk
+    if (huge != 0) rot_scale_rows<T>(buf, N, huge, 0.25f, tid);
     V acc[KC];
     const int c = tid / NSEG, sg = tid - c * NSEG;  // chunk and segment of this thread
     const V* seg = buf + sg * B;
@@ -182,6 +230,7 @@ __device__ __forceinline__ void rot_odd_factor_fixed(V* buf, int tid) {
       }
     }
     lds_barrier();
+    if (huge != 0) rot_scale_rows<T>(buf, N, huge, 4.f, tid);
   }
 }
 

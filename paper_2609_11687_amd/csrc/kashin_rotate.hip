@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "kashin.h"
 #include "kashin_internal.h"
@@ -37,13 +38,13 @@ __device__ __forceinline__ float to_float(bf16_t v) { return bf16_to_f32(v); }
 
 // R's factors without signs and scale, or R^T's
 template <int B, bool INV, bool PAD>
-__device__ __forceinline__ void rot_factors(float* buf, int n, int tid) {
+__device__ __forceinline__ void rot_factors(float* buf, int n, uint32_t huge, int tid) {
   if constexpr (!INV) {
-    rot_odd_factor<B, false, kRotThreads>(buf, n, tid);
+    rot_odd_factor<B, false, kRotThreads>(buf, n, huge, tid);
     rot_hadamard<B, kRotThreads, PAD>(buf, n, tid);
   } else {
     rot_hadamard<B, kRotThreads, PAD>(buf, n, tid);
-    rot_odd_factor<B, true, kRotThreads>(buf, n, tid);
+    rot_odd_factor<B, true, kRotThreads>(buf, n, 0, tid);
   }
 }
 
@@ -58,6 +59,7 @@ template <int B, bool INV, bool PAD, int K, class IT>
 __global__ __launch_bounds__(kRotThreads) void rotate_kernel(int n, uint64_t seed, float scale, const IT* x,
                                                              int64_t ldx, float* y, int64_t ldy, int64_t m) {
   extern __shared__ float buf[];  // n floats, or n + n/16 with PAD (padded slots, rot_slot)
+  static_assert(!rot_watch_huge<B, INV>(), "b = 1 and 3 only");
   const int tid = threadIdx.x;
   static_assert(K <= 32, "sign bits per thread");
   IT v[K];
@@ -82,7 +84,7 @@ __global__ __launch_bounds__(kRotThreads) void rotate_kernel(int n, uint64_t see
     }
     if (row + gridDim.x < m) load_row(row + gridDim.x);
     lds_barrier();
-    rot_factors<B, INV, PAD>(buf, n, tid);
+    rot_factors<B, INV, PAD>(buf, n, 0, tid);
     float* yr = y + row * ldy;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -103,6 +105,9 @@ template <int B, bool INV, bool PAD, class IT>
 __global__ __launch_bounds__(kRotThreads) void rotate_long_kernel(int n, uint64_t seed, float scale, const IT* x,
                                                                   int64_t ldx, float* y, int64_t ldy, int64_t row0) {
   extern __shared__ float buf[];
+  constexpr bool WATCH = rot_watch_huge<B, INV>() && !std::is_same<IT, __half>::value;  // no fp16 value is huge
+  __shared__ uint32_t flags[kRotThreads / 64];
+  bool huge = false;
   const int tid = threadIdx.x;
   const int64_t row = row0 + blockIdx.x;
   const IT* xr = x + row * ldx;
@@ -116,11 +121,15 @@ __global__ __launch_bounds__(kRotThreads) void rotate_long_kernel(int n, uint64_
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {
       const int i = i0 + k * kRotThreads;
+      if constexpr (WATCH) huge |= fabsf(v[k]) >= kRotHuge;
       if (i < n) buf[rot_slot<PAD>(i)] = INV ? v[k] : v[k] * rot_sign(seed, i);
     }
   }
+  if constexpr (WATCH) rot_note_huge(flags, huge, tid);
   lds_barrier();
-  rot_factors<B, INV, PAD>(buf, n, tid);
+  uint32_t huge_rows = 0;
+  if constexpr (WATCH) huge_rows = rot_huge_rows<kRotThreads / 64>(flags);
+  rot_factors<B, INV, PAD>(buf, n, huge_rows, tid);
   float* yr = y + row * ldy;
   for (int i = tid; i < n; i += kRotThreads) {
     const float v = buf[rot_slot<PAD>(i)] * scale;

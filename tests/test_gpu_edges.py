@@ -47,6 +47,48 @@ def test_rotate_rows_equal_single_rows(n, m, inverse):
     assert np.abs(got - want).max() <= 64 * 2.0 ** -24 * max(np.abs(want).max(), np.abs(x).max())
 
 
+@pytest.mark.parametrize("n", [3, 96, 768, 6144, 43, 172, 1376, 11008])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rotate_entries_near_the_largest_float(n, dtype):
+    """Rows whose odd-factor pair sums exceed the largest float while their products do not: finite and
+    the oracle's in both directions, the rows beside them as if alone, and the fused rotation as the
+    separate one."""
+    print(f"rotate near the largest float n={n} {dtype}", flush=True)
+    b = n // (n & -n)
+    big = 3.3e38
+    x = np.random.default_rng(n).standard_normal((7, n)).astype(np.float32)
+    x[[1, 2, 4, 5]] = 0.0
+    # norms below the largest float, so that no product overflows; pair sums or differences of 1.4 big
+    x[1, [0, b - 1]] = 0.7 * big
+    x[2, [n - b, n - 1]] = 0.7 * big, -0.7 * big
+    x[4, 1], x[4, [0, b - 1]] = -0.2 * big, 0.68 * big
+    x[5, n - b:] = np.where(np.arange(b) % 2, -1.0, 1.0) * big / 16
+    x[5, 0] = 2.0 ** 125
+    xd = pu.to_dev(x, torch.float32 if dtype == "f32" else torch.bfloat16)
+    x64 = xd.float().cpu().numpy().astype(np.float64)
+    for inverse in (False, True):
+        y = torch.empty((7, n), device="cuda")
+        K.kashin_rotate(n, 9, xd, y, inverse=inverse)
+        alone = torch.empty((1, n), device="cuda")
+        for r in (0, 3, 6):
+            K.kashin_rotate(n, 9, xd[r:r + 1], alone, inverse=inverse)
+            assert torch.equal(alone[0], y[r])
+        got, want = y.cpu().numpy(), ref.rotate(x64, 9, inverse=inverse)
+        # 64 roundings of the row's largest entries bound the rotation's error (see above)
+        assert np.isfinite(got).all()
+        assert (np.abs(got - want).max(axis=1) <= 64 * 2.0 ** -24 * np.abs(x64).max(axis=1)).all()
+    if n >= 96 and K.kashin_supported_n(n):
+        y = torch.empty((7, n), device="cuda")
+        K.kashin_rotate(n, 9, xd, y)
+        plan = K.kashin_plan(n, 4, 3)
+        sep = K.quantize_alloc(plan, y)
+        fused = [torch.empty_like(t) for t in sep]
+        K.kashin_quantize_rotated(plan, 9, xd, 0, *fused)
+        torch.cuda.synchronize()
+        for s, f in zip(sep, fused):
+            assert torch.equal(s.view(torch.uint8), f.view(torch.uint8))
+
+
 @pytest.mark.parametrize("n,d_in,chunk", [(11008, 500, 100), (4096, 1200, 128), (4096, 1129, 33), (10000, 520, 1)])
 def test_update_tiles(n, d_in, chunk):
     """The trailing update after one chunk against float64, at sizes with ragged tiles that take the
