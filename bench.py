@@ -843,8 +843,10 @@ def main() -> int:
     else:
         achieved = dom_bytes / dom_s / 1e9
         kname = f"rotate_kernel[b={dom_n // (dom_n & -dom_n)}]" if main_kind == "rotate" else "pair_pmap_kernel"
-        # rows up to 4096 long are walked by at most 2048 resident workgroups, longer ones take one each
-        grid = (lambda l: min(l.rows, 2048) if l.n <= 4096 else l.rows) if main_kind == "rotate" else (
+        # rows 2^a up to 4096 and 2^a 3 up to 2048 long are walked by at most 2048 resident workgroups, others
+        # take one each
+        walked = lambda n: n // (n & -n) == 1 and n <= 4096 or n // (n & -n) == 3 and n <= 2048  # noqa: E731
+        grid = (lambda l: min(l.rows, 2048) if walked(l.n) else l.rows) if main_kind == "rotate" else (
             lambda l: l.wgs or min((l.rows + 1) // 2, PMAP_GRID))
         keyn = (lambda l: 0) if main_kind == "rotate" else (lambda l: l.n)  # the rotation kernel takes n at run time
         roofline = {

@@ -13,7 +13,7 @@ from paper_2609_11687_amd import kashin as K
 pytestmark = pytest.mark.gpu
 
 
-# n at and around the element counts per thread that are compiled (1, 4, 8, 12, 16 times 256 entries),
+# n at and around the element counts per thread that are compiled (1, 4, 8, 16 times 256 entries),
 # the padded and unpadded layouts, every odd part; m above and below the resident workgroups
 # (at most 2048), so that workgroups take no, one or several rows
 @pytest.mark.parametrize("n,m", [(1, 3), (3, 5), (43, 4), (128, 2100), (256, 4500), (384, 2049), (512, 2047), (1024, 2100),
