@@ -12,7 +12,9 @@ namespace kashin {
 // The occupancy target is the one that measured best per length: 128 registers (four waves) pay at
 // 5120 and 6144, whose five- and six-wave workgroups otherwise leave SIMDs short; at 4096 and
 // 3072 three waves without spills beat four with; 8192 takes 256 threads of 32 values, whose
-// inner pass keeps every wave busy, over 512 of 16 (y = P x: 195 against 311 us).
+// inner pass keeps every wave busy, over 512 of 16 (y = P x: 195 against 311 us); 3072 has 64 threads more
+// than its 192 outer butterflies, so that each takes one of its 256 inner ones (16 rows, k = 10, 117.0 ->
+// 102.9 us, step schedules 6 to 12 % faster; 10922 rows 949 -> 1008, 1088 before the three-pass path).
 #define KASHIN_SIZES(X)         \
   X(64, 64, 2, 8, 8)            \
   X(96, 64, 2, 16, 3, 2)        \
@@ -22,7 +24,7 @@ namespace kashin {
   X(768, 64, 3, 16, 3, 16)      \
   X(1024, 64, 3, 16, 4, 16)     \
   X(2048, 128, 3, 16, 8, 16)    \
-  X(3072, 192, 3, 16, 12, 16)   \
+  X(3072, 256, 3, 16, 12, 16)   \
   X(4096, 256, 3, 16, 16, 16)   \
   X(5120, 320, 4, 16, 20, 16)   \
   X(6144, 384, 4, 16, 24, 16)   \

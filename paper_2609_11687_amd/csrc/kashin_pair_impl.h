@@ -1573,15 +1573,24 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
     trc = a.tr_c + item * steps;
   }
   // block-0 step sizes (equal in every lane): on the shapes whose block loop sits at its register
-  // limit they wait for the epilogue in LDS rather than in registers across the loop
-  constexpr bool CS_LDS = C::RES && (C::R0 > 16 || C::W >= 4 || (C::M & (C::M - 1)) != 0);
+  // limit they wait for the epilogue in LDS rather than in registers across the loop, and so they do in
+  // the instance that reports them, with thread 0 keeping the sums of the step sizes there too where a
+  // workgroup has several waves (in registers both spilled 5 to 11 of them at 1024, 2048 and 4096: 128
+  // rows, k = 10, 1024 wide 91.3 -> 85.7 us, 2048 wide 106.1 -> 100.4; a single wave waits for the sums:
+  // 512 wide 43.8 -> 45.6)
+  constexpr bool CS_LDS = C::RES && (!QUANT || C::R0 > 16 || C::W >= 4 || (C::M & (C::M - 1)) != 0);
   __shared__ float2 cs_lds[4];
   float2 cs_reg[4];
   float2* cs = CS_LDS ? cs_lds : cs_reg;
-  float2 csum_u = make_float2(0.f, 0.f), csum_v = make_float2(0.f, 0.f);
+  constexpr bool CSUM_LDS = !QUANT && C::RES && C::T > 64;
+  __shared__ float2 csum_lds[2];  // of the u-steps and the vhat-steps; thread 0's own
+  float2 csum_reg[2];
+  float2* csum = CSUM_LDS ? csum_lds : csum_reg;
+  if (!CSUM_LDS || threadIdx.x == 0) csum[0] = csum[1] = make_float2(0.f, 0.f);
   auto step = [&](int t, int st, float2 c) {
     if (t == 0 && (!CS_LDS || threadIdx.x == 0)) cs[st] = c;
     if constexpr (!QUANT) {
+      if (!CSUM_LDS || threadIdx.x == 0) csum[st >> 1] = cadd(csum[st >> 1], c);
       if (trc != nullptr && threadIdx.x == 0) trc[4 * t + st] = (side ? c.y : c.x) * (side ? unscale.y : unscale.x);
     }
   };
@@ -1592,19 +1601,15 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
     int8_t* tr = trace ? trace + int64_t(4 * t) * C::N : nullptr;
     float2 c = greedy_step<C, false>(z, vh, red, slot, tr, side);
     step(t, 0, c);
-    csum_u = cadd(csum_u, c);
     c = greedy_step<C, false>(z, vh, red, slot, tr ? tr + C::N : nullptr, side);
     step(t, 1, c);
-    csum_u = cadd(csum_u, c);
   };
   auto half_v = [&](int t) {
     int8_t* tr = trace ? trace + int64_t(4 * t + 2) * C::N : nullptr;
     float2 c = greedy_step<C, true>(z, vh, red, slot, tr, side);
     step(t, 2, c);
-    csum_v = cadd(csum_v, c);
     c = greedy_step<C, true>(z, vh, red, slot, tr ? tr + C::N : nullptr, side);
     step(t, 3, c);
-    csum_v = cadd(csum_v, c);
   };
   if constexpr (has_split_pass<C>()) {
     // one copy of P's code (see split_pass)
@@ -1707,13 +1712,13 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
       float* bo = a.bounds + ra * 4;
       bo[0] = bad_a ? qnan : mx[0] * unscale.x;
       bo[1] = bad_a ? qnan : mx[1] * unscale.x;
-      bo[2] = bad_a ? qnan : csum_u.x * unscale.x;
-      bo[3] = bad_a ? qnan : csum_v.x * unscale.x;
+      bo[2] = bad_a ? qnan : csum[0].x * unscale.x;
+      bo[3] = bad_a ? qnan : csum[1].x * unscale.x;
       if (rb >= 0) {
         bo[4] = bad_b ? qnan : mx[2] * unscale.y;
         bo[5] = bad_b ? qnan : mx[3] * unscale.y;
-        bo[6] = bad_b ? qnan : csum_u.y * unscale.y;
-        bo[7] = bad_b ? qnan : csum_v.y * unscale.y;
+        bo[6] = bad_b ? qnan : csum[0].y * unscale.y;
+        bo[7] = bad_b ? qnan : csum[1].y * unscale.y;
       }
     }
   }
