@@ -1467,18 +1467,20 @@ __device__ __forceinline__ void write_codes(const float2 (&x)[C::E], const float
     cb[C::N + i] = static_cast<uint8_t>(code_of(x[e].y, mids[1]));
   });
   lds_barrier();
-  constexpr int NBY = (C::N + 3) / 4;
-  for (int b = threadIdx.x; b < NBY; b += C::T) {
+  static_assert(C::N % 4 == 0, "four codes a byte");
+  constexpr int NBY = C::N / 4;
+  constexpr int K = (NBY + C::T - 1) / C::T;  // bytes per thread and row, unrolled: no read waits for another
+  const uint32_t* cw = reinterpret_cast<const uint32_t*>(lds);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int b = threadIdx.x + k * C::T;
+    if (NBY % C::T != 0 && b >= NBY) continue;
 #pragma unroll
     for (int sd = 0; sd < 2; ++sd) {
       const int64_t row = sd ? rb : ra;
       if (row < 0) continue;
-      uint32_t byte = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int i = 4 * b + k;
-        if (C::N % 4 == 0 || i < C::N) byte |= static_cast<uint32_t>(cb[sd * C::N + i] & 3) << (2 * k);
-      }
+      const uint32_t c = cw[sd * NBY + b];  // one code in the low bits of each byte
+      const uint32_t byte = c | (c >> 6) | (c >> 12) | (c >> 18);
       dst[row * NBY + b] = (sd ? bad_b : bad_a) ? 0 : static_cast<uint8_t>(byte);
     }
   }
@@ -1758,8 +1760,9 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
   __shared__ __align__(16) float2 lds[C::LDS + small_tw_total<C>()];
   __shared__ float red[2 * C::NW * 32];
   constexpr int N = C::N;
-  constexpr int NBY = (N + 3) / 4;
   static_assert(N % 4 == 0, "row staging in 16-byte vectors");
+  constexpr int NBY = N / 4;
+  constexpr int KQ = (NBY + C::T - 1) / C::T;  // code bytes per thread and row
   int slot = 0;
   constexpr bool RES = resident_ok<C>();
   ResRegs<C> rr;
@@ -1794,6 +1797,17 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
     const int64_t ra = 2 * (item0 + it);
     const int64_t rb = (ra + 1 < a.m) ? ra + 1 : -1;
     const int tid = opaque(threadIdx.x);
+    // a thread's bytes of both rows' codes, all loads issued before the first is used: a loop that loads,
+    // decodes and stores byte by byte waits for memory KQ times (at 8192, where a thread has eight, 16 rows
+    // 24.1 -> 21.5 us and 4096 rows 118 -> 95; 4096 wide, 8192 rows 73.3 -> 65.5)
+    auto load_codes = [&](const uint8_t* ca, const uint8_t* cb, uint32_t(&ba)[KQ], uint32_t(&bb)[KQ]) {
+#pragma unroll
+      for (int k = 0; k < KQ; ++k) {
+        const int q = tid + k * C::T;
+        ba[k] = ca[NBY % C::T == 0 || q < NBY ? q : NBY - 1];
+        bb[k] = cb[NBY % C::T == 0 || q < NBY ? q : NBY - 1];
+      }
+    };
     float2 z[C::E];
 #pragma unroll
     for (int e = 0; e < C::E; ++e) z[e] = make_float2(0.f, 0.f);
@@ -1808,8 +1822,13 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
       const float qb[4] = {ceb[0], ceb[1], ceb[2], ceb[3]};
       const uint8_t* cva = a.in_codes_v + ra * NBY;
       const uint8_t* cvb = a.in_codes_v + (rb >= 0 ? rb : ra) * NBY;
-      for (int q = tid; q < NBY; q += C::T) {
-        const uint32_t ba = cva[q], bb = cvb[q];
+      uint32_t bva[KQ], bvb[KQ];
+      load_codes(cva, cvb, bva, bvb);
+#pragma unroll
+      for (int k = 0; k < KQ; ++k) {
+        const int q = tid + k * C::T;
+        if (NBY % C::T != 0 && q >= NBY) continue;
+        const uint32_t ba = bva[k], bb = bvb[k];
         float4 va, vb;
         va.x = pick4(qa, ba & 3);
         va.y = pick4(qa, (ba >> 2) & 3);
@@ -1859,8 +1878,13 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
       const float* ceb = a.in_centers + (rb >= 0 ? rb : ra) * 8;
       const float ua[4] = {cea[0], cea[1], cea[2], cea[3]};
       const float ub[4] = {ceb[0], ceb[1], ceb[2], ceb[3]};
-      for (int q = tid; q < NBY; q += C::T) {
-        const uint32_t ba = cua[q], bb = cub[q];
+      uint32_t bua[KQ], bub[KQ];
+      load_codes(cua, cub, bua, bub);
+#pragma unroll
+      for (int j = 0; j < KQ; ++j) {
+        const int q = tid + j * C::T;
+        if (NBY % C::T != 0 && q >= NBY) continue;
+        const uint32_t ba = bua[j], bb = bub[j];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           float2 v = lds[4 * q + k];
@@ -1874,8 +1898,10 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
       rot_odd_factor_fixed<B, true, C::T, N>(lds, 0, tid);
       float* ya = a.y + ra * a.ldy;
       float* yb = a.y + (rb >= 0 ? rb : ra) * a.ldy;
-      for (int i = tid; i < N; i += C::T) {
-        const float s = rot_sign(a.rot_seed, i);
+      uint64_t st = rot_state(a.rot_seed, tid);
+#pragma unroll 4
+      for (int i = tid; i < N; i += C::T, st += C::T * kRotStep) {
+        const float s = rot_sign_of(st);
         const float2 v = lds[i];
         ya[i] = v.x * a.rot_scale * s;
         if (rb >= 0) yb[i] = v.y * a.rot_scale * s;
@@ -1898,9 +1924,14 @@ __global__ __launch_bounds__(C::T) __attribute__((amdgpu_waves_per_eu(C::W))) vo
     const float ub[4] = {ceb[0], ceb[1], ceb[2], ceb[3]};
     float* ya = a.y + ra * a.ldy;
     float* yb = a.y + (rb >= 0 ? rb : ra) * a.ldy;
-    for (int q = tid; q < N / 4; q += C::T) {
+    uint32_t bua[KQ], bub[KQ];
+    load_codes(cua, cub, bua, bub);
+#pragma unroll
+    for (int k = 0; k < KQ; ++k) {
+      const int q = tid + k * C::T;
+      if (NBY % C::T != 0 && q >= NBY) continue;
       float4 oa = lf4[q], ob = lf4[N / 4 + q];
-      const uint32_t ba = cua[q], bb = cub[q];
+      const uint32_t ba = bua[k], bb = bub[k];
       oa.x += pick4(ua, ba & 3);
       oa.y += pick4(ua, (ba >> 2) & 3);
       oa.z += pick4(ua, (ba >> 4) & 3);

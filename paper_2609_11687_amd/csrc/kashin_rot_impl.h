@@ -22,14 +22,19 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// s_i: -1 when the top bit of the i-th splitmix64 output of `seed` is set
-__device__ __forceinline__ float rot_sign(uint64_t seed, int i) {
-  uint64_t z = seed + static_cast<uint64_t>(i + 1) * 0x9E3779B97F4A7C15ull;
+// s_i: -1 when the top bit of the i-th splitmix64 output of `seed` is set: rot_sign_of(rot_state(seed, i)), and
+// rot_state(seed, i + d) = rot_state(seed, i) + d kRotStep (one of three 64-bit products saved)
+constexpr uint64_t kRotStep = 0x9E3779B97F4A7C15ull;
+__device__ __forceinline__ uint64_t rot_state(uint64_t seed, int i) {
+  return seed + static_cast<uint64_t>(i + 1) * kRotStep;
+}
+__device__ __forceinline__ float rot_sign_of(uint64_t z) {
   z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
   z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
   z ^= z >> 31;
   return (z >> 63) ? -1.f : 1.f;
 }
+__device__ __forceinline__ float rot_sign(uint64_t seed, int i) { return rot_sign_of(rot_state(seed, i)); }
 
 __device__ __forceinline__ float rv_fma(float c, float a, float acc) { return fmaf(c, a, acc); }
 __device__ __forceinline__ float2 rv_fma(float c, float2 a, float2 acc) {
