@@ -2018,17 +2018,19 @@ __device__ __forceinline__ void store_pair_staged(float2* lds, float* out_a, flo
 // row's signs, step sizes, choices and ||rho||^2 after every step.
 //
 // Where the workgroup shape caps the registers (more than 512 threads: one workgroup per CU, 168
-// VGPRs) or an array has 32 complex values, the arrays do not fit; vhat then lives in private memory
-// between its steps (16-byte loads and stores of the whole array at each vhat-step), so that the
-// residual's two domains and the transform's array stay in registers.
+// VGPRs) or an array has 32 complex values, the arrays do not fit, and vhat lives outside the registers
+// between its steps, so that the residual's two domains and the transform's array stay in them: in LDS
+// where there is room (sched_vh_lds_values), else (13824, 14336, 16384) in private memory, read and
+// written in 16 bytes, the whole array at each vhat-step.
 template <class C>
 constexpr bool sched_vh_in_memory() {
   return (C::T > 512 || C::E >= 32) && C::E % 2 == 0;
 }
-// Where LDS has room beside the transform's buffer (N = 11008: one element per butterfly thread,
-// B0 = 1), vhat lives there instead, as many of each thread's 2E values as fit (row a's first, then
-// row b's; each thread its own slots, read and written only at vhat-steps), the rest in registers:
-// private memory would be written back to HBM at every vhat-step.
+// vhat values a thread keeps in LDS beside the transform's buffer, of its 2E (row a's first, then row
+// b's; each thread its own slots, touched only at vhat-steps), the rest in registers; 0 if less than row
+// a's fit.  8192 keeps all 64 there (134 KB with the buffer: one workgroup of four waves a CU, no spills; k = 10,
+// 4096 rows 4114 us, against 5683 for the four passes on 512 threads with vhat in registers), 11008 those
+// that fit.  Private memory would be written back to HBM at every vhat-step.
 template <class C>
 constexpr int sched_vh_lds_values() {
   if constexpr (!sched_vh_in_memory<C>() || C::B0 != 1) {

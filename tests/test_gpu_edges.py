@@ -1,5 +1,6 @@
 """GPU tests at the edges of kernel variants: rows walked by resident workgroups in the rotation,
-the two tile sizes of the compensation's trailing update, and the error of the greedy kernels' own P."""
+the two tile sizes of the compensation's trailing update, the error of the greedy kernels' own P, the
+schedule kernel's storage of vhat per length, and rows that are not finite in the P-only kernels."""
 import numpy as np
 import pytest
 import scipy.fft
@@ -8,6 +9,7 @@ torch = pytest.importorskip("torch")
 
 import oracle.kashin_ref as ref
 import parity_util as pu
+import test_gpu_parity as parity
 from paper_2609_11687_amd import kashin as K
 
 pytestmark = pytest.mark.gpu
@@ -159,3 +161,69 @@ def test_operator_error(n):
     c, c_p = np.sqrt(num / den) / unit, np.sqrt(num_p / den_p) / unit
     print(f"c = {c:.3f}, P x {c_p:.3f}", flush=True)
     assert c <= 0.865 and c_p <= 1.02
+
+
+# where the schedule kernel keeps vhat: registers (256, 5120, 6144), all in LDS (8192), private memory
+# (13824, 14336, 16384; at 14336 with threads that hold no elements)
+@pytest.mark.parametrize("n,schedule", [(256, "adaptive"), (5120, "original"), (6144, "adaptive"), (8192, "adaptive"),
+                                        (8192, "reverse"), (13824, "original"), (13824, "alternating"),
+                                        (14336, "adaptive"), (16384, "original")])
+def test_schedule_storage_replay_parity(n, schedule):
+    """Five rows (an unpaired last one), every step replayed by the oracle; the traced call, which writes
+    no residual, equals the untraced one bit for bit."""
+    print(f"schedule storage n={n} {schedule}", flush=True)
+    parity.test_schedule_replay_parity(n, schedule)
+
+
+@pytest.mark.parametrize("n", [96, 256, 3072, 5120, 8192, 10000, 11008, 13824, 14336, 16384])
+@pytest.mark.parametrize("schedule", ["alternating", "adaptive"])
+def test_schedule_without_residual(n, schedule):
+    """u and vhat of many pairs without an r output equal those with one bit for bit."""
+    print(f"schedule without residual n={n} {schedule}", flush=True)
+    m = 701
+    w = torch.randn((m, n), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda") * 0.02
+    plan = K.kashin_plan(n, 3, 2)
+    u, v, r, u2, v2 = (torch.empty_like(w) for _ in range(5))
+    K.kashin_decompose_schedule(plan, schedule, w, u, v, r)
+    K.kashin_decompose_schedule(plan, schedule, w, u2, v2)
+    torch.cuda.synchronize()
+    assert torch.equal(u, u2) and torch.equal(v, v2)
+
+
+# the generic path (172), a single wave, several waves, the split pass, radix 32
+@pytest.mark.parametrize("n", [172, 512, 4096, 11008, 16384])
+def test_p_only_rows_that_are_not_finite(n):
+    """y = P x, the reconstruction and its rotated form: a row with a NaN or an infinity is all NaN, and its
+    partner is what it is beside a row of zeros, bit for bit."""
+    print(f"not finite n={n}", flush=True)
+    m = 9  # bad rows in either half of a pair, both halves, and the unpaired last row
+    bad = {1: float("nan"), 2: float("inf"), 4: -float("nan"), 5: -float("inf"), 8: float("nan")}
+    x = pu.to_dev(np.random.default_rng(n).standard_normal((m, n)).astype(np.float32))
+    clean = x.clone()
+    for i, (row, val) in enumerate(bad.items()):
+        x[row, (i * 37) % n] = val
+        clean[row] = 0.0
+    plan = K.kashin_plan(n, 4, 3)
+
+    def check(got, want):
+        torch.cuda.synchronize()
+        rows = [i for i in range(m) if i not in bad]
+        assert bool(torch.isnan(got[list(bad)]).all())
+        assert torch.equal(got[rows], want[rows]) and bool(torch.isfinite(got[rows]).all())
+
+    y, yc = torch.empty_like(x), torch.empty_like(x)
+    K.kashin_apply_p(plan, x, y)
+    K.kashin_apply_p(plan, clean, yc)
+    check(y, yc)
+    cu, cv, ce = K.quantize_alloc(plan, clean)
+    for row, val in bad.items():  # every entry of vhat a centre that is not finite
+        ce[row, 1] = 0.0
+    ce_bad = ce.clone()
+    for row, val in bad.items():
+        ce_bad[row, 1] = val
+    K.kashin_reconstruct(plan, cu, cv, ce_bad, y)
+    K.kashin_reconstruct(plan, cu, cv, ce, yc)
+    check(y, yc)
+    K.kashin_reconstruct_rotated(plan, 9, cu, cv, ce_bad, y)
+    K.kashin_reconstruct_rotated(plan, 9, cu, cv, ce, yc)
+    check(y, yc)
