@@ -71,8 +71,8 @@ void make_signs(int32_t n, uint64_t seed, int8_t* out) {
 }
 
 // Tables of the pair kernel for length n (layout shared with kashin_pair_impl.h):
-//  tw:  one table per Stockham pass with stride NS > 1 -- forward passes 1..np-1, then
-//       inverse passes 1..np-1 (radices in reverse order) -- entry [jm][r] =
+//  tw:  one table per Stockham pass with stride NS > 1 -- forward passes 1..np-1, then, on the generic
+//       path, inverse passes 1..np-1 (radices in reverse order) -- entry [jm][r] =
 //       exp(-2 pi i r jm / (NS R)), each table padded to an even length;
 //  mid: for the first inverse pass (radix R = last forward radix, stride 1), entry j R + r
 //       for element k = j + r n/R: Y'_k = f_k Y_s(k) with s(k) = k and f_k = eps_k / D when
@@ -95,7 +95,8 @@ void build_tables(int n, const int8_t* eps, std::vector<float2>* tw, std::vector
     for (int i = 0; i < q; ++i) ns *= sh.rad[i];
     add_table(sh.rad[q], ns);
   }
-  for (int q = 1; q < sh.np; ++q) {  // inverse passes
+  const bool generic = !kashin::three_pass(n, sh.threads, sh.np, sh.rad);
+  for (int q = 1; generic && q < sh.np; ++q) {  // inverse passes
     int ns = 1;
     for (int i = 0; i < q; ++i) ns *= sh.rad[sh.np - 1 - i];
     add_table(sh.rad[sh.np - 1 - q], ns);
@@ -121,7 +122,7 @@ void build_tables(int n, const int8_t* eps, std::vector<float2>* tw, std::vector
         fy = float(ek * std::sin(ang) / div);
         src = partner;
       }
-      const int addr = kashin::pad_slot(n, src) * int(sizeof(float2));
+      const int addr = kashin::pad_slot(src) * int(sizeof(float2));  // read on the generic path only
       float faddr;
       std::memcpy(&faddr, &addr, sizeof(faddr));
       (*mid)[j * R + r] = make_float4(fx, fy, faddr, float(ek));

@@ -155,10 +155,17 @@ constexpr double p_divisor(int n, int r0, int m) {
   return (n > 4096 && m <= 32) ? n * (1.0 + 2.0 * (2.0 * dft_gain(r0) + dft_gain(m))) : n;
 }
 
-// LDS layout of the generic path's transform buffer: element i of a length-n vector lives at float2
-// slot i + (i >> pad_shift(n)).
-__host__ __device__ constexpr int pad_shift(int n) { return n % 512 == 0 ? 5 : 4; }
-__host__ __device__ constexpr int pad_slot(int n, int i) { return i + (i >> pad_shift(n)); }
+// Whether a shape (threads per workgroup, np radices) takes the three-pass path: n = r0 m r0, r0 even, one
+// butterfly of the outer passes per thread.  The inverse runs the same radices on the same tables there
+// and the frequency factors are addressed by the thread's own elements.
+constexpr bool three_pass(int n, int threads, int np, const int* rad) {
+  return np == 3 && rad[0] == rad[2] && rad[0] % 2 == 0 && threads >= n / rad[0];
+}
+
+// LDS layout of the generic path's transform buffer: element i of the vector lives at float2 slot
+// i + (i >> kPadShift).
+constexpr int kPadShift = 4;
+constexpr int pad_slot(int i) { return i + (i >> kPadShift); }
 
 bool supported_n(int n);
 // Launch the pair kernel for vector length n; grid = number of work items (pairs or listed rows).

@@ -332,15 +332,14 @@ struct Cfg {
   static constexpr int B0 = (NB0 + T - 1) / T;
   static constexpr int E = B0 * R0;
   static constexpr int NW = (T + 63) / 64;
-  static constexpr int PS = pad_shift(N_);  // generic path: a spare LDS slot per 2^PS elements
-  static constexpr int PG = 1 << PS;
+  static constexpr int PG = 1 << kPadShift;  // generic path: a spare LDS slot per PG elements
   // three-pass path (N = R0 M R0, one butterfly of the outer passes per thread)
-  static constexpr bool RES = NP == 3 && rad[0] == rad[NP - 1] && R0 % 2 == 0 && B0 == 1;
+  static constexpr bool RES = three_pass(N_, T_, NP, rad);
   static constexpr int M = RES ? rad[1] : 1;
   static constexpr bool UNI = RES && M == R0 && (R0 & (R0 - 1)) == 0;  // one power-of-two radix throughout
   static constexpr int S1 = NB0 + (R0 == 8 ? 4 : 2);   // row strides of the two exchange layouts (below)
   static constexpr int S2 = NB0 + (R0 == 20 ? 8 : 1);
-  static constexpr int LDS = RES ? R0 * (S1 > S2 ? S1 : S2) + 2 : N + (N >> PS) + 4;
+  static constexpr int LDS = RES ? R0 * (S1 > S2 ? S1 : S2) + 2 : pad_slot(N) + 4;
 };
 
 template <class C>
@@ -361,7 +360,7 @@ constexpr int ns_inv(int p) {
 // pass spread over the banks).  pad<C>(x + y) = pad<C>(x) + pad<C>(y) whenever x mod PG +
 // y mod PG < PG: a base slot plus compile-time offsets addresses a butterfly's elements.
 template <class C>
-__host__ __device__ constexpr int pad(int i) { return i + (i >> C::PS); }
+constexpr int pad(int i) { return pad_slot(i); }
 // Whether a Stockham write (element q of butterfly j to b + q S, b = (j / S) S R + j mod S,
 // q < R) can address slots as pad(b) + pad(q S): S a multiple of PG, or S dividing PG with
 // S R a multiple or a divisor of PG (then b mod PG + q S mod PG < PG for every q).
@@ -508,7 +507,7 @@ __device__ __forceinline__ void block_max(float (&v)[K], float* red, int& slot) 
 }
 
 // ------------------------------------------------------------------ plan tables
-// Twiddle tables, one per pass with stride NS > 1, forward passes first then inverse
+// Twiddle tables, one per pass with stride NS > 1, forward passes first then (generic path) inverse
 // passes: entry [jm][r] = w_N^(r * jm * N / (NS R)), jm < NS, r < R (each table padded to
 // an even length so every table starts 16-byte aligned).  Every thread reads its R
 // twiddles contiguously.
