@@ -6,9 +6,10 @@ namespace kashin {
 // Supported vector lengths: N, threads per workgroup, occupancy target (waves per SIMD),
 // forward radices.  From 256 up N = R0 M R0 on the three-pass path; quantising rows (k = 30, us)
 // against the shapes before it, which took four or five passes with the tables in memory:
-//   5120 (16384 rows)  21640 -> 9245     10000 (4096)  9150 -> 5180     14336 (4096) 11960 -> 6620
-//   6144 (8192)        12580 -> 5250     13824 (4096) 14900 -> 7200     16384 (4096)  9330 -> 6570
-//   8192 (8192)        14760 -> 5790     256 (8192)     472 -> 208
+//   5120 (16384 rows)  21610 -> 9220     10000 (4096)  9160 -> 5140     14336 (4096) 11950 -> 6580
+//   6144 (8192)        12560 -> 5230     13824 (4096) 14880 -> 6930     16384 (4096)  9290 -> 6490
+//   8192 (8192)        14770 -> 5770     256 (8192)     473 -> 215      3072 (8192)   2220 -> 2040
+// and with two k-means passes 13824, whose 168 registers spill 200 there, 15180 -> 9800, 11008 7620 -> 7080.
 // The occupancy target is the one that measured best per length: 128 registers (four waves) pay at
 // 5120 and 6144, whose five- and six-wave workgroups otherwise leave SIMDs short; at 4096 and
 // 3072 three waves without spills beat four with; 8192 takes 256 threads of 32 values, whose

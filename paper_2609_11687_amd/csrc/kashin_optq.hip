@@ -171,8 +171,8 @@ __global__ __launch_bounds__(kGT) void update_gemm_kernel(float* c, int64_t ldc,
 }
 
 // The same product in 128 x 128 tiles: 256 threads with 8 x 8 accumulators each (rows tr .. tr + 3 and
-// 64 + tr .., columns likewise: 16-byte LDS reads, a quarter of the words per FMA of the 4 x 4
-// tile's), the next K step's tile loaded into registers while this one is multiplied.  Every
+// 64 + tr .., columns likewise: 16-byte LDS reads, a quarter of a word per FMA where the 4 x 4 tile
+// reads half a word), the next K step's tile loaded into registers while this one is multiplied.  Every
 // accumulator runs over k in the same order as above: the results are equal bit for bit.  128 x
 // (3968 x 4096): 84 -> 79 us; a whole chunk step with 11008-long rows 1223 -> 1113.  (128 x 128 tiles
 // on the FP32 matrix instruction took 75 us at the one and made the other 1150.)

@@ -672,9 +672,10 @@ __device__ __forceinline__ void apply_P(float2 (&z)[C::E], float2* lds, const fl
 // 64-lane 8-byte write costs the CU 6.5 clocks, an 8-byte read 4, and a 16-byte read, measured at
 // twice the bytes per clock, 4.4, against about 190 two-clock instructions of a radix-16 butterfly
 // over four SIMDs.  One larger inner radix (M = 20, 24, 25, 32) beats two small ones even where
-// some waves idle in it.  Each exchange has a layout of its own, in which every access is free of
-// bank conflicts (8-byte reads resolve per 32 lanes over 64 banks, 8-byte writes per 16 lanes over
-// 32) except a few for R0 = 20 and 24:
+// some waves idle in it.  Each exchange has a layout of its own, in which the accesses of the passes are
+// free of bank conflicts (8-byte reads resolve per 32 lanes over 64 banks, 8-byte writes per 16 lanes
+// over 32) except a few for R0 = 20 and 24; the eps step's partner reads, 8 bytes at a lane stride of 16,
+// conflict two ways (2.5 % of the CU's cycles at N = 4096; read as 16-byte pairs they cost more):
 //   first -> inner   element i = R0 t + q (output q of butterfly t) at slot q S1 + t: written in
 //                    lane order; butterfly (jh, jm) of the inner pass reads input r at
 //                    jm S1 + jh + r R0, its lanes running over jm and the low bit of jh
@@ -751,7 +752,7 @@ __device__ __forceinline__ float2 cmulf(float2 x, float2 y) {
 // w_{4a} w_b (one rounding) of the kept powers 1, 2, 3, 4, 8, 12, ..  Only the split shape keeps no
 // more than 1 and 4, from which w^15 takes five products: at 5120 and 6144 that put P's error up by
 // 10 and 7 % (rms 18.9e-8 and 19.5e-8 of the input against 17.0e-8 and 18.1e-8), for 0.2 and 1.2 % of
-// the quantiser's time (the four more powers spill 27 and 22 registers).
+// the quantiser's time (it spills 21 and 33 registers; with two powers 1 and 21).
 template <class C, class RR>
 constexpr bool kept_tw(int r) {
   return C::R0 < 16 ? r > 0 : (RR::compact ? (r == 1 || r == 4) : r > 0 && (r < 4 || r % 4 == 0));
