@@ -227,3 +227,37 @@ def test_p_only_rows_that_are_not_finite(n):
     K.kashin_reconstruct_rotated(plan, 9, cu, cv, ce_bad, y)
     K.kashin_reconstruct_rotated(plan, 9, cu, cv, ce, yc)
     check(y, yc)
+
+
+def test_long_schedule_replays_and_repeats():
+    """200 updates at N = 10^4, far past the point where the residual is rounding: the oracle replayed on the
+    GPU's near-tie signs gives the same factors (a sign taken otherwise at such an entry moves whole factors by
+    1e-3 to 1e-2, so that two correct builds differ by as much), and the call repeats itself bit for bit."""
+    n, k, m = 10000, 50, 12
+    print("long schedule", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    wd = torch.randn((m, n), generator=g, device="cuda") * 0.02
+    plan = K.kashin_plan(n, 21, k)
+    u, v, r, u2, v2, ut, vt = (torch.empty_like(wd) for _ in range(7))
+    K.kashin_decompose_schedule(plan, "alternating", wd, u, v, r)
+    for fill in (0.0, 7.0):
+        u2.fill_(fill)
+        v2.fill_(fill)
+        K.kashin_decompose_schedule(plan, "alternating", wd, u2, v2, r)
+        assert torch.equal(u, u2) and torch.equal(v, v2)
+    rows = torch.arange(m, dtype=torch.int64, device="cuda")
+    sg = torch.empty((m, 4 * k, n), dtype=torch.int8, device="cuda")
+    cs, r2 = (torch.empty((m, 4 * k), device="cuda") for _ in range(2))
+    ch = torch.empty((m, 4 * k), dtype=torch.int8, device="cuda")
+    K.kashin_trace_schedule(plan, "alternating", wd, rows, sg, cs, ch, r2, ut, vt)
+    torch.cuda.synchronize()
+    assert torch.equal(u, ut) and torch.equal(v, vt)
+    w = wd.cpu().numpy().astype(np.float64)
+    winf = np.abs(w).max(axis=1)
+    rep = ref.decompose_schedule(w, ref.sign_mask(n, 21), 4 * k, "alternating", replay_signs=sg.cpu().numpy(),
+                                 replay_choices=ch.cpu().numpy(), tau=pu.TAU_REL * winf, choice_band=1e-5)
+    du = (np.abs(u.cpu().numpy() - rep["u"]).max(axis=1) / winf).max()
+    dv = (np.abs(v.cpu().numpy() - rep["vhat"]).max(axis=1) / winf).max()
+    print(f"du={du:.2e} dv={dv:.2e}", flush=True)
+    assert not rep["replay_outside"].any()
+    assert du <= pu.TOL_FACTOR and dv <= pu.TOL_FACTOR
